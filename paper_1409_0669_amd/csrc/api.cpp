@@ -132,24 +132,37 @@ bwla_config lookup(int op, int t, int acc, double bytes)
 
 bool is_pow2(int v) { return v > 0 && (v & (v - 1)) == 0; }
 
-// Largest pack width (elements, power of two, <= want) such that every address
-// in `ptrs` and every line stride `ld` keeps packs aligned.
-int fit_vec(int want, size_t esize, std::initializer_list<const void *> ptrs, int64_t ld = 0)
+// Pack width: `want` for vectors and matrices whose elements are aligned to
+// their size, wherever they start and whatever the leading dimension (the
+// kernels' packs need no more; device.hpp has both sides' times); single
+// elements otherwise.
+int fit_vec(int want, size_t esize, std::initializer_list<const void *> ptrs)
 {
-    int v = want;
-    while (v > 1) {
-        bool ok = true;
-        for (const void *p : ptrs)
-            if (p && ((uintptr_t)p % (v * esize)) != 0)
-                ok = false;
-        if (ld && (ld % v) != 0)
-            ok = false;
-        if (ok)
-            break;
-        v >>= 1;
-    }
-    return v;
+    for (const void *p : ptrs)
+        if ((uintptr_t)p % esize != 0)
+            return 1;
+    return want;
 }
+
+// Elements of a vector operation before its first pack.  With every vector on
+// a pack boundary, none.  Otherwise as many as bring the first of `ptrs` (the
+// written vector, or a reduction's first) to a 128-byte cache line: a wave's
+// 1 KiB of stores then fills whole lines, and slices that all start alike
+// read aligned packs too.  Fewer than 64, the smallest work-group.
+int pack_head(int vec, size_t esize, int64_t n, std::initializer_list<const void *> ptrs)
+{
+    bool aligned = true;
+    for (const void *p : ptrs)
+        aligned = aligned && (uintptr_t)p % (vec * esize) == 0;
+    if (aligned || vec == 1)
+        return 0;
+    const uintptr_t past = (uintptr_t)*ptrs.begin() % 128;
+    return (int)std::min<int64_t>(n, past ? (int64_t)((128 - past) / esize) : 0);
+}
+
+// Addresses that stand for a call's operands when a workspace is sized: one
+// that no element is aligned to (single elements) and one that every pack is.
+const void *const kFakes[2] = {(const void *)(uintptr_t)1, (const void *)(uintptr_t)256};
 
 bwla_status check_cfg(const bwla_config &c)
 {
@@ -185,6 +198,7 @@ Cfg resolve_vector(int op, int t, int acc, int64_t n, std::initializer_list<cons
     Cfg c;
     c.block = u.block ? u.block : 256;
     c.vec = fit_vec(u.vec ? u.vec : native_vec(t), dsize(t), ptrs);
+    c.head = pack_head(c.vec, dsize(t), n, ptrs);
     c.unroll = u.unroll ? u.unroll : (op == BWLA_OP_DOT || op == BWLA_OP_NRM2 ? 4 : 1);
     if (c.unroll > 4 && op != BWLA_OP_DOT && op != BWLA_OP_NRM2)
         c.unroll = 4; // eight packs in flight exist for the reductions (and the cols GEMV) only
@@ -211,12 +225,12 @@ Cfg resolve_vector(int op, int t, int acc, int64_t n, std::initializer_list<cons
     return c;
 }
 
-Cfg resolve_rows(int t, int acc, int64_t L, int64_t K, const void *A, int64_t ld, const void *v)
+Cfg resolve_rows(int t, int acc, int64_t L, int64_t K, const void *A, const void *v)
 {
     bwla_config u = lookup(BWLA_OP_GEMV_ROWS, t, acc, (double)L * K * dsize(t));
     Cfg c;
     c.block = u.block ? u.block : 1024;
-    c.vec = fit_vec(u.vec ? u.vec : native_vec(t), dsize(t), {A, v}, ld);
+    c.vec = fit_vec(u.vec ? u.vec : native_vec(t), dsize(t), {A, v});
     c.unroll = u.unroll == 2 ? 2 : 1; // packs of each line in flight per thread: 1 or 2
     c.inc = 0;
     c.rows = u.rows ? u.rows : 2;
@@ -246,13 +260,12 @@ Cfg resolve_rows(int t, int acc, int64_t L, int64_t K, const void *A, int64_t ld
     return c;
 }
 
-Cfg resolve_cols(int t, int acc, int64_t L, int64_t K, const void *A, int64_t ld, const void *v)
+Cfg resolve_cols(int t, int acc, int64_t L, int64_t K, const void *A)
 {
-    (void)v; // x is staged element by element: its alignment does not constrain the pack width
     bwla_config u = lookup(BWLA_OP_GEMV_COLS, t, acc, (double)L * K * dsize(t));
     Cfg c;
     c.block = u.block ? u.block : 512;
-    c.vec = fit_vec(u.vec ? u.vec : native_vec(t), dsize(t), {A}, ld);
+    c.vec = fit_vec(u.vec ? u.vec : native_vec(t), dsize(t), {A});
     c.unroll = u.unroll ? u.unroll : 4; // lines in flight per wave: 1 to 32
     while (c.unroll > 8 && (size_t)c.unroll * c.vec * dsize(t) > kColsLoadBytes)
         c.unroll /= 2; // more would spill: at most kColsLoadBytes of A in flight per lane
@@ -278,18 +291,17 @@ Cfg resolve_cols(int t, int acc, int64_t L, int64_t K, const void *A, int64_t ld
     return c;
 }
 
-Cfg resolve_ger(int t, int64_t L, int64_t K, const void *a, const void *b, const void *A, int64_t ld)
+Cfg resolve_ger(int t, int64_t L, int64_t K, const void *b, const void *A)
 {
     bwla_config u = lookup(BWLA_OP_GER, t, BWLA_ACC_PLAIN, (double)L * K * dsize(t));
     Cfg c;
     c.block = u.block ? u.block : 256;
-    c.vec = fit_vec(u.vec ? u.vec : native_vec(t), dsize(t), {b, A}, ld);
+    c.vec = fit_vec(u.vec ? u.vec : native_vec(t), dsize(t), {b, A});
     c.unroll = 1;
     c.grid = 0;
     c.inc = 0;
     c.rows = u.rows ? u.rows : 4;
     c.split = 1;
-    (void)a;
     return c;
 }
 
@@ -872,9 +884,9 @@ static size_t gemv_ws(const GemvPlan &g, const Cfg &c, bool with_dot, size_t *dp
     return base + (size_t)gemv_dot_parts(g.rows, g.L, g.K, c) * sizeof(DD);
 }
 
-static Cfg gemv_cfg(bwla_dtype t, int acc, const GemvPlan &g, const void *A, int64_t lda, const void *x)
+static Cfg gemv_cfg(bwla_dtype t, int acc, const GemvPlan &g, const void *A, const void *x)
 {
-    return g.rows ? resolve_rows(t, acc, g.L, g.K, A, lda, x) : resolve_cols(t, acc, g.L, g.K, A, lda, x);
+    return g.rows ? resolve_rows(t, acc, g.L, g.K, A, x) : resolve_cols(t, acc, g.L, g.K, A);
 }
 
 // Shared body of bwla_gemv and bwla_gemv_dot (w == NULL: no epilogue).
@@ -938,7 +950,7 @@ static bwla_status gemv_common(bwla_dtype t, bwla_acc acc, bwla_layout layout, i
     }
     const bool comp = acc == BWLA_ACC_COMPENSATED;
     const int of64 = out_t == BWLA_F64, df64 = dot_t == BWLA_F64;
-    Cfg c = gemv_cfg(t, acc, g, A, lda, x);
+    Cfg c = gemv_cfg(t, acc, g, A, x);
     size_t off = 0;
     const size_t need = gemv_ws(g, c, fused, &off);
     if (need && (!ws || ws_bytes < need))
@@ -992,10 +1004,8 @@ bwla_status bwla_gemv_dot_workspace_size(bwla_dtype t, bwla_layout layout, int t
         return BWLA_OK; // only fills run
     size_t best = 0; // largest over the pack widths and accumulation modes the call could use
     for (int acc = 0; acc < kAccs; ++acc)
-        for (int v = 1; v <= 16; v <<= 1) {
-            const void *fake = (const void *)(uintptr_t)(v * dsize(t));
-            best = std::max(best, gemv_ws(g, gemv_cfg(t, acc, g, fake, v, fake), true, nullptr));
-        }
+        for (const void *fake : kFakes)
+            best = std::max(best, gemv_ws(g, gemv_cfg(t, acc, g, fake, fake), true, nullptr));
     *bytes = best;
     return BWLA_OK;
 }
@@ -1052,7 +1062,7 @@ bwla_status bwla_gemv_ex(bwla_dtype t, bwla_acc acc, bwla_layout layout, int tra
     Cfg c{};
     size_t need = off_g;
     if (g.in_len > 0) {
-        c = gemv_cfg(t, acc, g, A, lda, xs);
+        c = gemv_cfg(t, acc, g, A, xs);
         need += gemv_ws(g, c, false, nullptr);
     }
     if (!ws || ws_bytes < need)
@@ -1119,10 +1129,8 @@ bwla_status bwla_gemv_ex_workspace_size(bwla_dtype t, bwla_dtype out_t, bwla_lay
     size_t gw = 0;
     if (g.in_len > 0)
         for (int acc = 0; acc < kAccs; ++acc)
-            for (int v = 1; v <= 16; v <<= 1) {
-                const void *fake = (const void *)(uintptr_t)(v * dsize(t));
-                gw = std::max(gw, gemv_ws(g, gemv_cfg(t, acc, g, fake, v, fake), false, nullptr));
-            }
+            for (const void *fake : kFakes)
+                gw = std::max(gw, gemv_ws(g, gemv_cfg(t, acc, g, fake, fake), false, nullptr));
     *bytes = best + gw;
     return BWLA_OK;
 }
@@ -1150,7 +1158,7 @@ bwla_status bwla_ger(bwla_dtype t, bwla_layout layout, int64_t m, int64_t n, con
         return fail(BWLA_ERR_INVALID_ARG, "A overlaps u or v");
     const void *a = row_major ? u : v; // per-line factor
     const void *b = row_major ? v : u; // factor along the line
-    Cfg c = resolve_ger(t, L, K, a, b, A, lda);
+    Cfg c = resolve_ger(t, L, K, b, A);
     hipError_t e = by_type(t, [&](auto *tag) {
         using T = std::remove_pointer_t<decltype(tag)>;
         return launch_ger<T>(L, K, a, b, A, lda, c, (hipStream_t)stream);
@@ -1203,15 +1211,13 @@ bwla_status bwla_workspace_size(bwla_op op, bwla_dtype t, bwla_acc acc, bwla_lay
         return fail(BWLA_ERR_INVALID_ARG, "negative size");
     *bytes = 0;
     // The pack width a call ends up with depends on pointer alignment, and the
-    // default grid and split depend on the pack width, so size for the largest
-    // requirement over every width the call could use.  A fake address
-    // v*sizeof(T) (and line stride v) is aligned to exactly v elements.  The
-    // size also serves the other accumulation mode, whose table entry may
-    // differ, so a buffer sized once serves both.
+    // default grid and split depend on the pack width, so size for the larger
+    // requirement of the two widths the call could use (kFakes).  The size
+    // also serves the other accumulation mode, whose table entry may differ,
+    // so a buffer sized once serves both.
     size_t best = 0;
     for (int a = 0; a < kAccs; ++a) {
-        for (int v = 1; v <= 16; v <<= 1) {
-            const void *fake = (const void *)(uintptr_t)(v * dsize(t));
+        for (const void *fake : kFakes) {
             switch (op) {
             case BWLA_OP_DOT: // dot, nrm2, asum (any increments) and the CG update share one sizing
             case BWLA_OP_NRM2:
@@ -1229,9 +1235,9 @@ bwla_status bwla_workspace_size(bwla_op op, bwla_dtype t, bwla_acc acc, bwla_lay
                 if (g.out_len == 0 || g.in_len == 0)
                     break; // no kernel runs
                 if (g.rows)
-                    best = std::max(best, ws_rows(resolve_rows(t, a, g.L, g.K, fake, v, fake), g.L));
+                    best = std::max(best, ws_rows(resolve_rows(t, a, g.L, g.K, fake, fake), g.L));
                 else
-                    best = std::max(best, ws_cols(resolve_cols(t, a, g.L, g.K, fake, v, fake), g.K));
+                    best = std::max(best, ws_cols(resolve_cols(t, a, g.L, g.K, fake), g.K));
                 break;
             }
             default:
@@ -1288,9 +1294,9 @@ bwla_status bwla_get_config(bwla_op op, bwla_dtype t, bwla_acc acc, int64_t m, i
     case BWLA_OP_DOT: c = resolve_vector(op, t, acc, n, {}, 2); break;
     case BWLA_OP_NRM2: c = resolve_vector(op, t, acc, n, {}, 1); break;
     case BWLA_OP_CG: c = resolve_vector(op, t, acc, n, {}, 6); break;
-    case BWLA_OP_GEMV_ROWS: c = resolve_rows(t, acc, m, n, nullptr, 0, nullptr); break;
-    case BWLA_OP_GEMV_COLS: c = resolve_cols(t, acc, m, n, nullptr, 0, nullptr); break;
-    case BWLA_OP_GER: c = resolve_ger(t, m, n, nullptr, nullptr, nullptr, 0); break;
+    case BWLA_OP_GEMV_ROWS: c = resolve_rows(t, acc, m, n, nullptr, nullptr); break;
+    case BWLA_OP_GEMV_COLS: c = resolve_cols(t, acc, m, n, nullptr); break;
+    case BWLA_OP_GER: c = resolve_ger(t, m, n, nullptr, nullptr); break;
     case BWLA_OP_BATCH: c = resolve_batch(t, acc, (double)n); break;
     default: return fail(BWLA_ERR_INVALID_ARG, "op %d", op);
     }
@@ -1441,7 +1447,7 @@ bwla_status bwla_batch_plan_create(bwla_dtype t, bwla_acc acc, bwla_dtype out_t,
             Span sy = span(q.y, q.m * os);
             if (overlaps(sy, span(q.A, matrix_bytes(q.m, q.n, q.lda, es))) || overlaps(sy, span(q.x, q.n * es)))
                 return fail(BWLA_ERR_INVALID_ARG, "gemv %d: y overlaps A or x", i);
-            if (fit_vec(nv, es, {q.A, q.x}, q.lda) != nv)
+            if (fit_vec(nv, es, {q.A, q.x}) != nv)
                 aligned = false;
         }
     }
@@ -1499,13 +1505,13 @@ bwla_status bwla_batch_plan_create(bwla_dtype t, bwla_acc acc, bwla_dtype out_t,
         b.y = q.y;
         // grouped launch: x staged in LDS when it fits (rows at any
         // alignment; measured as fast as, or faster than, x in registers on
-        // aligned rows), else 16-byte packs of every operand when A's rows
-        // and x are 16-byte aligned, else one element per access
+        // aligned rows), else 16-byte packs of every operand, or one element
+        // per access when A or x is not aligned to its elements
         int v_item = p->vec;
         if (!p->persistent) {
             if (q.n <= tile_stage_elems((int)es))
                 b.mode = kModeStaged, v_item = nv;
-            else if (q.m > 0 && q.n > 0 && fit_vec(nv, es, {q.A, q.x}, q.lda) == nv)
+            else if (q.m > 0 && q.n > 0 && fit_vec(nv, es, {q.A, q.x}) == nv)
                 b.mode = kModePacked, v_item = nv;
             else
                 b.mode = kModeScalar, v_item = 1;

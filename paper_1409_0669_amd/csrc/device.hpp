@@ -34,94 +34,73 @@ __device__ __forceinline__ float fma_c(float a, float b, float c) { return __bui
 // ---------------------------------------------------------------------------
 // Packed global memory access: V consecutive elements per thread.  Packs of
 // 16 bytes or more are moved as 16-byte (dwordx4) accesses; smaller packs as
-// one 8/4/2-byte access.  Callers guarantee alignment to V*sizeof(T).
+// one 8/4/2-byte access.  A pack may start on any element: the word types
+// below claim the smallest element's alignment only, and the compiler still issues
+// one dwordx4 for them, because gfx950 runs with unaligned global access enabled.
+// What a misaligned pack costs is the extra cache line that a wave's 1 KiB
+// then touches; element-wide accesses, to which a misaligned operand once fell
+// back, cost 2 (f64) to 8 (bf16) times the instructions.  Measured, element
+// accesses against packs: slices of 10^7 bf16, axpby 32.0 -> 12.3 us, copy 15.4
+// -> 8.8, dot 14.6 -> 8.3, nrm2 9.3 -> 4.8; y = A x with rows of an odd length,
+// 8001 x 8003 bf16 32.2 -> 24.9 us, 5001 x 5003 f64 38.5 -> 34.5 us, and the
+// transposed bf16 product 41.8 -> 29.0 us.
 // ---------------------------------------------------------------------------
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t word4 __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint32_t word2 __attribute__((ext_vector_type(2), aligned(2)));
+typedef uint32_t word1 __attribute__((aligned(2)));
 
 template <typename T, int V> struct Pack {
     T v[V];
 };
 
-template <typename T, int V>
+// NT: the nontemporal hint, for data touched exactly once -- vector operands,
+// the matrix of a GEMV, outputs.  It keeps once-read streams from displacing
+// reusable lines in the caches; measured on MI355X, copy goes from ~6.0 to
+// ~6.6 TB/s and a read-only stream from ~6.3 to ~7.0 TB/s.
+// (A function each: a template parameter would drop the type's alignment.)
+#define BWLA_WORD(W)                                                                                   \
+    template <bool NT> __device__ __forceinline__ W load_##W(const W *p)                               \
+    {                                                                                                  \
+        if constexpr (NT)                                                                              \
+            return __builtin_nontemporal_load(p);                                                      \
+        else                                                                                           \
+            return *p;                                                                                 \
+    }                                                                                                  \
+    __device__ __forceinline__ void store_nt_##W(W *p, W v) { __builtin_nontemporal_store(v, p); }
+BWLA_WORD(word4)
+BWLA_WORD(word2)
+BWLA_WORD(word1)
+BWLA_WORD(uint16_t)
+#undef BWLA_WORD
+
+template <typename T, int V, bool NT = false>
 __device__ __forceinline__ Pack<T, V> load_pack(const T *p)
 {
     constexpr int B = V * (int)sizeof(T);
     Pack<T, V> r;
     if constexpr (B >= 16) {
-        const u32x4 *s = reinterpret_cast<const u32x4 *>(p);
-        u32x4 tmp[B / 16];
+        const auto *s = reinterpret_cast<const word4 *>(p);
+        word4 tmp[B / 16];
 #pragma unroll
         for (int i = 0; i < B / 16; ++i)
-            tmp[i] = s[i];
+            tmp[i] = load_word4<NT>(s + i);
         __builtin_memcpy(&r, tmp, B);
     } else if constexpr (B == 8) {
-        u32x2 tmp = *reinterpret_cast<const u32x2 *>(p);
+        const word2 tmp = load_word2<NT>(reinterpret_cast<const word2 *>(p));
         __builtin_memcpy(&r, &tmp, B);
     } else if constexpr (B == 4) {
-        uint32_t tmp = *reinterpret_cast<const uint32_t *>(p);
+        const word1 tmp = load_word1<NT>(reinterpret_cast<const word1 *>(p));
         __builtin_memcpy(&r, &tmp, B);
     } else {
-        uint16_t tmp = *reinterpret_cast<const uint16_t *>(p);
+        const uint16_t tmp = load_uint16_t<NT>(reinterpret_cast<const uint16_t *>(p));
         __builtin_memcpy(&r, &tmp, B);
     }
     return r;
 }
-
-template <typename T, int V>
-__device__ __forceinline__ void store_pack(T *p, const Pack<T, V> &r)
-{
-    constexpr int B = V * (int)sizeof(T);
-    if constexpr (B >= 16) {
-        u32x4 tmp[B / 16];
-        __builtin_memcpy(tmp, &r, B);
-        u32x4 *d = reinterpret_cast<u32x4 *>(p);
-#pragma unroll
-        for (int i = 0; i < B / 16; ++i)
-            d[i] = tmp[i];
-    } else if constexpr (B == 8) {
-        u32x2 tmp;
-        __builtin_memcpy(&tmp, &r, B);
-        *reinterpret_cast<u32x2 *>(p) = tmp;
-    } else if constexpr (B == 4) {
-        uint32_t tmp;
-        __builtin_memcpy(&tmp, &r, B);
-        *reinterpret_cast<uint32_t *>(p) = tmp;
-    } else {
-        uint16_t tmp;
-        __builtin_memcpy(&tmp, &r, B);
-        *reinterpret_cast<uint16_t *>(p) = tmp;
-    }
-}
-
-// Streaming (nontemporal) variants for data touched exactly once -- vector
-// operands, the matrix of a GEMV, outputs.  On gfx950 they set the
-// nontemporal hint on the 16-byte accesses, which keeps once-read streams
-// from displacing reusable lines in the caches; measured on MI355X, copy goes
-// from ~6.0 to ~6.6 TB/s and a read-only stream from ~6.3 to ~7.0 TB/s.
 template <typename T, int V>
 __device__ __forceinline__ Pack<T, V> load_pack_nt(const T *p)
 {
-    constexpr int B = V * (int)sizeof(T);
-    Pack<T, V> r;
-    if constexpr (B >= 16) {
-        const u32x4 *s = reinterpret_cast<const u32x4 *>(p);
-        u32x4 tmp[B / 16];
-#pragma unroll
-        for (int i = 0; i < B / 16; ++i)
-            tmp[i] = __builtin_nontemporal_load(s + i);
-        __builtin_memcpy(&r, tmp, B);
-    } else if constexpr (B == 8) {
-        u32x2 tmp = __builtin_nontemporal_load(reinterpret_cast<const u32x2 *>(p));
-        __builtin_memcpy(&r, &tmp, B);
-    } else if constexpr (B == 4) {
-        uint32_t tmp = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(p));
-        __builtin_memcpy(&r, &tmp, B);
-    } else {
-        uint16_t tmp = __builtin_nontemporal_load(reinterpret_cast<const uint16_t *>(p));
-        __builtin_memcpy(&r, &tmp, B);
-    }
-    return r;
+    return load_pack<T, V, true>(p);
 }
 
 // Ends the load phase of an unrolled trip: no instruction moves across it,
@@ -132,30 +111,47 @@ __device__ __forceinline__ Pack<T, V> load_pack_nt(const T *p)
 // packs for some compensated instantiations, halving their bandwidth.
 __device__ __forceinline__ void end_of_loads() { __builtin_amdgcn_sched_barrier(0); }
 
+// Streaming (nontemporal) store of a pack.
 template <typename T, int V>
 __device__ __forceinline__ void store_pack_nt(T *p, const Pack<T, V> &r)
 {
     constexpr int B = V * (int)sizeof(T);
     if constexpr (B >= 16) {
-        u32x4 tmp[B / 16];
+        word4 tmp[B / 16];
         __builtin_memcpy(tmp, &r, B);
-        u32x4 *d = reinterpret_cast<u32x4 *>(p);
+        auto *d = reinterpret_cast<word4 *>(p);
 #pragma unroll
         for (int i = 0; i < B / 16; ++i)
-            __builtin_nontemporal_store(tmp[i], d + i);
+            store_nt_word4(d + i, tmp[i]);
     } else if constexpr (B == 8) {
-        u32x2 tmp;
+        word2 tmp;
         __builtin_memcpy(&tmp, &r, B);
-        __builtin_nontemporal_store(tmp, reinterpret_cast<u32x2 *>(p));
+        store_nt_word2(reinterpret_cast<word2 *>(p), tmp);
     } else if constexpr (B == 4) {
-        uint32_t tmp;
+        word1 tmp;
         __builtin_memcpy(&tmp, &r, B);
-        __builtin_nontemporal_store(tmp, reinterpret_cast<uint32_t *>(p));
+        store_nt_word1(reinterpret_cast<word1 *>(p), tmp);
     } else {
         uint16_t tmp;
         __builtin_memcpy(&tmp, &r, B);
-        __builtin_nontemporal_store(tmp, reinterpret_cast<uint16_t *>(p));
+        store_nt_uint16_t(reinterpret_cast<uint16_t *>(p), tmp);
     }
+}
+
+// The elements of a vector outside its packs: `head` before the first pack
+// (negative indices from it, fewer than 64) and the last n - packed, all taken
+// by the first threads of work-group 0.  n and the indices count from the
+// first pack.
+template <typename F>
+__device__ __forceinline__ void edge_elements(int head, int64_t packed, int64_t n, F &&f)
+{
+    if (blockIdx.x != 0)
+        return;
+    const int t = (int)threadIdx.x;
+    if (t < head)
+        f((int64_t)t - head);
+    if (t < n - packed)
+        f(packed + t);
 }
 
 // ---------------------------------------------------------------------------

@@ -164,7 +164,11 @@ __global__ __launch_bounds__(1024) void k_gemv_cols(int64_t L, int64_t K, const 
     // below is one scalar load shared by the wave
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t k0 = tile * TK + (int64_t)lane * V;
-    const bool full = k0 + V <= K;
+    // The lane whose pack runs past the end of the lines takes the last V
+    // columns instead and keeps those from k0 on: the same loads and the same
+    // loop as its neighbours.  Taken element by element, that one lane made
+    // its waves three times as long (8001 x 8003 bf16: 107 us in all).
+    const int64_t kb = k0 + V <= K ? k0 : K - V;
     const int64_t per = (L + split - 1) / split;
     const int64_t lb = (int64_t)s * per;
     const int64_t le = lb + per < L ? lb + per : L;
@@ -176,10 +180,10 @@ __global__ __launch_bounds__(1024) void k_gemv_cols(int64_t L, int64_t K, const 
     // v[l] is read with the U lines' loads (no staging pass and no barrier
     // before the first loads of A).
     const T *vt = v + lb;
-    const T *base = A + lb * ld + k0;
+    const T *base = A + lb * ld + kb;
     const int64_t tn = le - lb;
     int64_t j = wave;
-    if (full) {
+    if (k0 < K && kb >= 0) {
         for (; j + (int64_t)(U - 1) * nw < tn; j += (int64_t)U * nw) {
             Pack<T, V> a[U];
             C xv[U];
@@ -202,12 +206,12 @@ __global__ __launch_bounds__(1024) void k_gemv_cols(int64_t L, int64_t K, const 
             for (int e = 0; e < V; ++e)
                 acc[e].template add_prod<EXACT>(widen(a.v[e]), xl);
         }
-    } else if (k0 < K) {
+    } else if (k0 < K) { // lines shorter than a pack
         for (; j < tn; j += nw) {
             const C xl = widen(vt[j]);
 #pragma unroll
             for (int e = 0; e < V; ++e)
-                if (k0 + e < K)
+                if (kb + e >= 0)
                     acc[e].template add_prod<EXACT>(widen(base[j * ld + e]), xl);
         }
     }
@@ -250,19 +254,19 @@ __global__ __launch_bounds__(1024) void k_gemv_cols(int64_t L, int64_t K, const 
     if (wave == 0) {
 #pragma unroll
         for (int e = 0; e < V; ++e) {
-            if (split == 1) {
-                if (k0 + e < K)
-                    store_out(out, k0 + e, out_f64, d[e].hi + d[e].lo);
-            } else {
-                partials[(tile * split + s) * TK + lane * V + e] = d[e];
-            }
+            if (kb + e < k0 || k0 >= K)
+                continue;
+            if (split == 1)
+                store_out(out, kb + e, out_f64, d[e].hi + d[e].lo);
+            else
+                partials[(tile * split + s) * TK + (kb + e - tile * TK)] = d[e];
         }
         if (w != nullptr && split == 1) {
             DD t = {0.0, 0.0};
 #pragma unroll
             for (int e = 0; e < V; ++e)
-                if (k0 + e < K)
-                    t = combine<COMP>(t, epilogue_term<C, COMP>(widen(w[k0 + e]), (C)(d[e].hi + d[e].lo)));
+                if (kb + e >= k0 && k0 < K)
+                    t = combine<COMP>(t, epilogue_term<C, COMP>(widen(w[kb + e]), (C)(d[e].hi + d[e].lo)));
             t = wave_sum<COMP>(t);
             if (lane == 0)
                 dparts[tile] = t;

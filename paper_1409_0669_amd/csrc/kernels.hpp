@@ -12,6 +12,7 @@ namespace bwla {
 // Resolved kernel configuration (no zero fields left).
 struct Cfg {
     int block, vec, unroll, grid, inc, rows, split;
+    int head = 0; // vector operations: elements before the first pack (see pack_head in api.cpp)
 };
 
 // The workspace of a reduction holds its float64 partials (DD pairs).
@@ -156,7 +157,7 @@ struct BatchItem {
 // plan-wide BatchArgs::vec instead).
 enum {
     kModeStaged = 0, // GEMV with n <= tile_stage_elems(): x staged in LDS, 16-byte packs of A
-    kModePacked = 1, // 16-byte packs of every operand (all of them 16-byte aligned)
+    kModePacked = 1, // 16-byte packs of every operand (elements aligned to their size)
     kModeScalar = 2  // one element per access
 };
 constexpr int kTileStageBytes = 32768; // most LDS a staged GEMV tile's x may take

@@ -27,11 +27,15 @@ __device__ __forceinline__ void reduce_term(Acc<C, COMP> &acc, C a, C b)
 
 template <typename T, int V, int U, bool COMP, int MODE>
 __global__ __launch_bounds__(1024) void k_dot(int64_t n, const T *x, const T *y, DD *partials,
-                                              void *out, int out_f64, int inc)
+                                              void *out, int out_f64, int inc, int head)
 {
     using C = compute_t<T>;
     constexpr bool EXACT = std::is_same<T, bf16_t>::value;
     Acc<C, COMP> acc[U];
+    x += head;
+    if constexpr (MODE == kRedDot)
+        y += head;
+    n -= head;
     const int64_t npack = n / V;
     int64_t begin, stride, end;
     const int64_t lb = xcd_block();
@@ -72,11 +76,9 @@ __global__ __launch_bounds__(1024) void k_dot(int64_t n, const T *x, const T *y,
         for (int e = 0; e < V; ++e)
             reduce_term<MODE, EXACT>(acc[0], widen(vx.v[e]), MODE == kRedDot ? widen(vy.v[e]) : C(0));
     }
-    const int64_t tail = n - npack * V;
-    if (blockIdx.x == 0 && threadIdx.x < tail) {
-        const int64_t i = npack * V + threadIdx.x;
+    edge_elements(head, npack * V, n, [&](int64_t i) {
         reduce_term<MODE, EXACT>(acc[0], widen(x[i]), MODE == kRedDot ? widen(y[i]) : C(0));
-    }
+    });
     DD v = acc[0].to_dd();
 #pragma unroll
     for (int u = 1; u < U; ++u)
@@ -154,7 +156,7 @@ hipError_t launch_dot(int64_t n, bool comp, int mode, const void *x, const void 
                 auto go = [&](auto M) {
                     hipLaunchKernelGGL((k_dot<T, V.value, U.value, CP.value, M.value>), dim3(c.grid),
                                        dim3(c.block), 0, s, n, (const T *)x, (const T *)y, partials,
-                                       out, out_f64, c.inc);
+                                       out, out_f64, c.inc, c.head);
                     return hipGetLastError();
                 };
                 switch (mode) {

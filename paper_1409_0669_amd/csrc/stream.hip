@@ -10,8 +10,10 @@
 // touched once).  The loop increment is either the whole grid (GLOBAL, the
 // paper's first skeleton) or the work-group inside one contiguous chunk per
 // work-group (LOCAL, the paper's second skeleton; chunks are multiples of the
-// work-group size so accesses stay aligned).  The n % V tail elements are
-// handled element-wise by the first threads of work-group 0.
+// work-group size so accesses stay aligned).  Vectors that start off a pack
+// boundary (slices) begin with `head` single elements, so that the packs of
+// the written vector start on a cache line whatever the others do; these and
+// the tail are handled element-wise by the first threads of work-group 0.
 #include "device.hpp"
 #include "kernels.hpp"
 
@@ -46,8 +48,11 @@ __device__ __forceinline__ Range pack_range(int64_t npack, int inc)
 // copy
 // ---------------------------------------------------------------------------
 template <typename T, int V, int U>
-__global__ __launch_bounds__(1024) void k_copy(int64_t n, const T *y, T *x, int inc)
+__global__ __launch_bounds__(1024) void k_copy(int64_t n, const T *y, T *x, int inc, int head)
 {
+    y += head;
+    x += head;
+    n -= head;
     const int64_t npack = n / V;
     Range rg = pack_range(npack, inc);
     int64_t p = rg.begin;
@@ -63,9 +68,7 @@ __global__ __launch_bounds__(1024) void k_copy(int64_t n, const T *y, T *x, int 
     }
     for (; p < rg.end; p += rg.stride)
         store_pack_nt<T, V>(x + p * V, load_pack_nt<T, V>(y + p * V));
-    const int64_t tail = n - npack * V;
-    if (blockIdx.x == 0 && threadIdx.x < tail)
-        x[npack * V + threadIdx.x] = y[npack * V + threadIdx.x];
+    edge_elements(head, npack * V, n, [&](int64_t i) { x[i] = y[i]; });
 }
 
 // ---------------------------------------------------------------------------
@@ -73,10 +76,13 @@ __global__ __launch_bounds__(1024) void k_copy(int64_t n, const T *y, T *x, int 
 // ---------------------------------------------------------------------------
 template <typename T, int V, int U>
 __global__ __launch_bounds__(1024) void k_scal(int64_t n, compute_t<T> a, const compute_t<T> *adev,
-                                               const T *y, T *x, int inc)
+                                               const T *y, T *x, int inc, int head)
 {
     if (adev)
         a = a * *adev;
+    y += head;
+    x += head;
+    n -= head;
     const int64_t npack = n / V;
     Range rg = pack_range(npack, inc);
     int64_t p = rg.begin;
@@ -101,11 +107,7 @@ __global__ __launch_bounds__(1024) void k_scal(int64_t n, compute_t<T> a, const 
             v.v[e] = narrow<T>(a * widen(v.v[e]));
         store_pack_nt<T, V>(x + p * V, v);
     }
-    const int64_t tail = n - npack * V;
-    if (blockIdx.x == 0 && threadIdx.x < tail) {
-        const int64_t i = npack * V + threadIdx.x;
-        x[i] = narrow<T>(a * widen(y[i]));
-    }
+    edge_elements(head, npack * V, n, [&](int64_t i) { x[i] = narrow<T>(a * widen(y[i])); });
 }
 
 // ---------------------------------------------------------------------------
@@ -121,12 +123,16 @@ __device__ __forceinline__ T axpby_elem(compute_t<T> a, T y, compute_t<T> b, T z
 template <typename T, int V, int U>
 __global__ __launch_bounds__(1024) void k_axpby(int64_t n, compute_t<T> a, const compute_t<T> *adev,
                                                 compute_t<T> b, const compute_t<T> *bdev, const T *y,
-                                                const T *z, T *x, int inc)
+                                                const T *z, T *x, int inc, int head)
 {
     if (adev)
         a = a * *adev;
     if (bdev)
         b = b * *bdev;
+    y += head;
+    z += head;
+    x += head;
+    n -= head;
     const int64_t npack = n / V;
     Range rg = pack_range(npack, inc);
     int64_t p = rg.begin;
@@ -154,11 +160,7 @@ __global__ __launch_bounds__(1024) void k_axpby(int64_t n, compute_t<T> a, const
             o.v[e] = axpby_elem<T>(a, vy.v[e], b, vz.v[e]);
         store_pack_nt<T, V>(x + p * V, o);
     }
-    const int64_t tail = n - npack * V;
-    if (blockIdx.x == 0 && threadIdx.x < tail) {
-        int64_t i = npack * V + threadIdx.x;
-        x[i] = axpby_elem<T>(a, y[i], b, z[i]);
-    }
+    edge_elements(head, npack * V, n, [&](int64_t i) { x[i] = axpby_elem<T>(a, y[i], b, z[i]); });
 }
 
 // ---------------------------------------------------------------------------
@@ -168,13 +170,18 @@ __global__ __launch_bounds__(1024) void k_axpby(int64_t n, compute_t<T> a, const
 template <typename T, int V, int U, bool COMP>
 __global__ __launch_bounds__(1024) void k_cg(int64_t n, compute_t<T> a, const compute_t<T> *adev, T *x,
                                              const T *p, T *r, const T *q, DD *partials, void *out,
-                                             int out_f64, int inc)
+                                             int out_f64, int inc, int head)
 {
     using C = compute_t<T>;
     constexpr bool EXACT = std::is_same<T, bf16_t>::value;
     if (adev)
         a = a * *adev;
     const C one = 1, na = -a;
+    x += head;
+    p += head;
+    r += head;
+    q += head;
+    n -= head;
     Acc<C, COMP> acc[U];
     const int64_t npack = n / V;
     Range rg = pack_range(npack, inc);
@@ -218,15 +225,13 @@ __global__ __launch_bounds__(1024) void k_cg(int64_t n, compute_t<T> a, const co
         store_pack_nt<T, V>(x + o, vx);
         store_pack_nt<T, V>(r + o, vr);
     }
-    const int64_t tail = n - npack * V;
-    if (blockIdx.x == 0 && threadIdx.x < tail) {
-        const int64_t o = npack * V + threadIdx.x;
+    edge_elements(head, npack * V, n, [&](int64_t o) {
         x[o] = axpby_elem<T>(a, p[o], one, x[o]);
         T rv = axpby_elem<T>(na, q[o], one, r[o]);
         r[o] = rv;
         C rn = widen(rv);
         acc[0].template add_prod<EXACT>(rn, rn);
-    }
+    });
     DD v = acc[0].to_dd();
 #pragma unroll
     for (int u = 1; u < U; ++u)
@@ -250,7 +255,7 @@ hipError_t launch_copy(int64_t n, const void *y, void *x, const Cfg &c, hipStrea
     return with_vec(c.vec, [&](auto V) {
         return with_unroll(c.unroll, [&](auto U) {
             hipLaunchKernelGGL((k_copy<T, V.value, U.value>), dim3(c.grid), dim3(c.block), 0, s, n,
-                               (const T *)y, (T *)x, c.inc);
+                               (const T *)y, (T *)x, c.inc, c.head);
             return hipGetLastError();
         });
     });
@@ -264,7 +269,7 @@ hipError_t launch_scal(int64_t n, double alpha, const void *adev, const void *y,
     return with_vec(c.vec, [&](auto V) {
         return with_unroll(c.unroll, [&](auto U) {
             hipLaunchKernelGGL((k_scal<T, V.value, U.value>), dim3(c.grid), dim3(c.block), 0, s, n, (C)alpha,
-                               (const C *)adev, (const T *)y, (T *)x, c.inc);
+                               (const C *)adev, (const T *)y, (T *)x, c.inc, c.head);
             return hipGetLastError();
         });
     });
@@ -279,7 +284,7 @@ hipError_t launch_axpby(int64_t n, double alpha, const void *adev, const void *y
         return with_unroll(c.unroll, [&](auto U) {
             hipLaunchKernelGGL((k_axpby<T, V.value, U.value>), dim3(c.grid), dim3(c.block), 0, s, n,
                                (C)alpha, (const C *)adev, (C)beta, (const C *)bdev, (const T *)y,
-                               (const T *)z, (T *)x, c.inc);
+                               (const T *)z, (T *)x, c.inc, c.head);
             return hipGetLastError();
         });
     });
@@ -297,7 +302,7 @@ hipError_t launch_cg(int64_t n, bool comp, double alpha, const void *adev, void 
             return with_bool(comp, [&](auto CP) {
                 hipLaunchKernelGGL((k_cg<T, V.value, U.value, CP.value>), dim3(c.grid), dim3(c.block),
                                    0, s, n, (C)alpha, (const C *)adev, (T *)x, (const T *)p, (T *)r,
-                                   (const T *)q, partials, out, out_f64, c.inc);
+                                   (const T *)q, partials, out, out_f64, c.inc, c.head);
                 return hipGetLastError();
             });
         });
