@@ -101,7 +101,10 @@ typedef enum BWLA_ENUM_INT {
  *   GEMV_ROWS:        block, vec, rows (lines per block), unroll (packs of each
  *                     line in flight: 1 or 2), split (blocks along a line), grid
  *   GEMV_COLS:        block, vec, unroll (lines in flight), split (blocks across
- *                     lines), grid
+ *                     lines), grid, rows (lines per wave access; above 1 the
+ *                     packs are 16 bytes wide).  An entry with no block,
+ *                     unroll, split, grid and rows leaves all of them to a
+ *                     rule that follows the matrix's shape
  *   GER:              block, vec, rows
  *   BATCH:            block (work-group size, at most 512), unroll (packs of a
  *                     GEMV row each lane of a staged tile owns: sets how many

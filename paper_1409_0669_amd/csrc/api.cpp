@@ -8,6 +8,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
@@ -160,9 +161,15 @@ int pack_head(int vec, size_t esize, int64_t n, std::initializer_list<const void
     return (int)std::min<int64_t>(n, past ? (int64_t)((128 - past) / esize) : 0);
 }
 
-// Addresses that stand for a call's operands when a workspace is sized: one
-// that no element is aligned to (single elements) and one that every pack is.
-const void *const kFakes[2] = {(const void *)(uintptr_t)1, (const void *)(uintptr_t)256};
+// Operands that stand for a call's when a workspace is sized: the three that
+// a configuration can depend on.  Elements not aligned to their size, lines on
+// cache lines, and lines that start anywhere.
+struct Fake {
+    const void *p;
+    int64_t ld;
+};
+const Fake kFakes[3] = {{(const void *)(uintptr_t)1, 1}, {(const void *)(uintptr_t)256, 128},
+                        {(const void *)(uintptr_t)256, 1}};
 
 bwla_status check_cfg(const bwla_config &c)
 {
@@ -260,18 +267,95 @@ Cfg resolve_rows(int t, int acc, int64_t L, int64_t K, const void *A, const void
     return c;
 }
 
-Cfg resolve_cols(int t, int acc, int64_t L, int64_t K, const void *A)
+// The cols kernels' shape when the table names none, from the matrix's own.
+//
+// Lines per wave access (rows) and split come from a cost in microseconds:
+//  - A CU streams about 30 GB/s whatever it has in flight (one work-group over
+//    16000 lines of 128 bytes: 70 us), so the time is that of the fullest CU:
+//    the bytes at 7.2 TB/s times how unevenly tiles * split work-groups fill 256.
+//  - More lines per access make the tile narrower, so that few columns fill
+//    the chip with less splitting, but shorten each line's segment from 512 (2
+//    lines) to 128 bytes (8): f32 16384 x 16384 154.6 us at 2 lines, 156 at 4, 171
+//    at 8; f64 306, 324, 347.  Lines that start off a cache line touch one
+//    more per segment: bf16 8001 x 8003 27.8, 33.4, 34.4.
+//  - A split costs the second kernel, 1.4 us of GPU time and 2 us of the
+//    host's (300 x 300 f64 in one launch 4.1 us, in two 5.2; before 8.5), and its
+//    partials, up to 1 us.
+// One work-group count per size class, as the table held before, gave f32
+// 16000 x 100 17.8 us where this gives 7.6, and 1200 x 1501 11.3 where this gives 6.6.
+//
+// Depth: small matrices and the compensated f32 and bf16 forms (vector-ALU
+// bound with 4 waves) run 512 threads with 4 lines each, the others 256 with 8.
+//
+// One line per access (k_gemv_cols) stays where it is the faster: plain f64
+// from 64 MiB and f32 from 1 GiB with lines on cache lines, 8 bytes per lane
+// (f64 16384 x 16384 298 us against 308, f32 151 against 155).
+Cfg cols_rule(int t, int acc, int64_t L, int64_t K, bool line_aligned)
+{
+    const bool comp = acc == BWLA_ACC_COMPENSATED, f64 = t == BWLA_F64;
+    const double bytes = (double)L * K * dsize(t);
+    Cfg c{};
+    auto tiles_of = [&](int lines) {
+        c.rows = lines;
+        return ceil_div(K, cols_tile(c));
+    };
+    if (!comp && line_aligned && t != BWLA_BF16 && bytes >= (f64 ? 64.0 : 1024.0) * (1 << 20)) {
+        const bool large = f64 && bytes >= 1073741824.0;
+        c.vec = (int)(8 / dsize(t));
+        c.unroll = 4;
+        c.block = large ? 512 : 1024;
+        c.split = (int)std::min<int64_t>(ceil_div(large ? 512 : 256, tiles_of(1)), std::max<int64_t>(1, L / 16));
+    } else {
+        // the cost of 512-, 256- and 128-byte segments
+        static const double kSegment[3][3] = {{1.0, 1.05, 1.12}, {1.02, 1.01, 1.08}, {1.0, 1.08, 1.15}};
+        const double *segment = kSegment[!line_aligned ? 2 : f64 ? 0 : 1];
+        c.vec = native_vec(t);
+        double best = 1e300;
+        int best_rows = 8;
+        int64_t best_split = 1;
+        for (int i = 0; i < 3; ++i) {
+            const int64_t tiles = tiles_of(2 << i);
+            for (int64_t fill = 0; fill <= 4; ++fill) { // one slice, or as many as fill the chip 1 to 4 times
+                const int64_t split = std::max<int64_t>(1, std::min(fill * 256 / tiles, L / 64));
+                const double groups = (double)tiles * (double)split;
+                const double uneven = ceil(groups / 256.0) * 256.0 / groups;
+                double us = bytes / 7.2e6 * segment[i] * uneven;
+                if (split > 1)
+                    us += 2.0 + 0.08 * (double)std::min<int64_t>(split, 8) + 0.02 * (double)split;
+                if (us < best) {
+                    best = us;
+                    best_rows = 2 << i;
+                    best_split = split;
+                }
+            }
+        }
+        c.rows = best_rows;
+        c.split = (int)best_split;
+        const bool deep = bytes >= 32.0 * (1 << 20) && (!comp || f64);
+        c.unroll = deep ? 8 : 4;
+        c.block = deep ? 256 : 512;
+    }
+    c.grid = (int)std::min<int64_t>(ceil_div(K, cols_tile(c)) * c.split, 0x7fffffff);
+    return c;
+}
+
+Cfg resolve_cols(int t, int acc, int64_t L, int64_t K, const void *A, int64_t ld)
 {
     bwla_config u = lookup(BWLA_OP_GEMV_COLS, t, acc, (double)L * K * dsize(t));
     Cfg c;
-    c.block = u.block ? u.block : 512;
     c.vec = fit_vec(u.vec ? u.vec : native_vec(t), dsize(t), {A});
+    const bool grouped = c.vec == native_vec(t) && K >= c.vec;
+    if (grouped && !u.block && !u.unroll && !u.grid && !u.rows && !u.split)
+        return cols_rule(t, acc, L, K, (uintptr_t)A % 128 == 0 && ld * (int64_t)dsize(t) % 128 == 0);
+    c.block = u.block ? u.block : 512;
     c.unroll = u.unroll ? u.unroll : 4; // lines in flight per wave: 1 to 32
     while (c.unroll > 8 && (size_t)c.unroll * c.vec * dsize(t) > kColsLoadBytes)
         c.unroll /= 2; // more would spill: at most kColsLoadBytes of A in flight per lane
     c.inc = 0;
-    c.rows = 1;
-    const int64_t tiles = std::max<int64_t>(1, ceil_div(K, 64 * (int64_t)c.vec));
+    c.rows = grouped && u.rows ? u.rows : 1;
+    if (c.rows == 2 && c.block / 64 * cols_tile(c) * (int64_t)sizeof(DD) > 49152)
+        c.rows = 4;
+    const int64_t tiles = std::max<int64_t>(1, ceil_div(K, cols_tile(c)));
     const int64_t waves = c.block / 64;
     int64_t split = u.split;
     if (!split && u.grid) {
@@ -333,7 +417,7 @@ size_t ws_cols(const Cfg &c, int64_t K)
 {
     if (c.split <= 1)
         return 0;
-    return (size_t)ceil_div(K, 64 * (int64_t)c.vec) * c.split * 64 * c.vec * sizeof(DD);
+    return (size_t)ceil_div(K, cols_tile(c)) * c.split * cols_tile(c) * sizeof(DD);
 }
 
 // Parses a tuning table ("op dtype acc size_class block vec unroll grid
@@ -884,9 +968,9 @@ static size_t gemv_ws(const GemvPlan &g, const Cfg &c, bool with_dot, size_t *dp
     return base + (size_t)gemv_dot_parts(g.rows, g.L, g.K, c) * sizeof(DD);
 }
 
-static Cfg gemv_cfg(bwla_dtype t, int acc, const GemvPlan &g, const void *A, const void *x)
+static Cfg gemv_cfg(bwla_dtype t, int acc, const GemvPlan &g, const void *A, int64_t lda, const void *x)
 {
-    return g.rows ? resolve_rows(t, acc, g.L, g.K, A, x) : resolve_cols(t, acc, g.L, g.K, A);
+    return g.rows ? resolve_rows(t, acc, g.L, g.K, A, x) : resolve_cols(t, acc, g.L, g.K, A, lda);
 }
 
 // Shared body of bwla_gemv and bwla_gemv_dot (w == NULL: no epilogue).
@@ -950,7 +1034,7 @@ static bwla_status gemv_common(bwla_dtype t, bwla_acc acc, bwla_layout layout, i
     }
     const bool comp = acc == BWLA_ACC_COMPENSATED;
     const int of64 = out_t == BWLA_F64, df64 = dot_t == BWLA_F64;
-    Cfg c = gemv_cfg(t, acc, g, A, x);
+    Cfg c = gemv_cfg(t, acc, g, A, lda, x);
     size_t off = 0;
     const size_t need = gemv_ws(g, c, fused, &off);
     if (need && (!ws || ws_bytes < need))
@@ -1004,8 +1088,8 @@ bwla_status bwla_gemv_dot_workspace_size(bwla_dtype t, bwla_layout layout, int t
         return BWLA_OK; // only fills run
     size_t best = 0; // largest over the pack widths and accumulation modes the call could use
     for (int acc = 0; acc < kAccs; ++acc)
-        for (const void *fake : kFakes)
-            best = std::max(best, gemv_ws(g, gemv_cfg(t, acc, g, fake, fake), true, nullptr));
+        for (const Fake &f : kFakes)
+            best = std::max(best, gemv_ws(g, gemv_cfg(t, acc, g, f.p, f.ld, f.p), true, nullptr));
     *bytes = best;
     return BWLA_OK;
 }
@@ -1062,7 +1146,7 @@ bwla_status bwla_gemv_ex(bwla_dtype t, bwla_acc acc, bwla_layout layout, int tra
     Cfg c{};
     size_t need = off_g;
     if (g.in_len > 0) {
-        c = gemv_cfg(t, acc, g, A, xs);
+        c = gemv_cfg(t, acc, g, A, lda, xs);
         need += gemv_ws(g, c, false, nullptr);
     }
     if (!ws || ws_bytes < need)
@@ -1129,8 +1213,8 @@ bwla_status bwla_gemv_ex_workspace_size(bwla_dtype t, bwla_dtype out_t, bwla_lay
     size_t gw = 0;
     if (g.in_len > 0)
         for (int acc = 0; acc < kAccs; ++acc)
-            for (const void *fake : kFakes)
-                gw = std::max(gw, gemv_ws(g, gemv_cfg(t, acc, g, fake, fake), false, nullptr));
+            for (const Fake &f : kFakes)
+                gw = std::max(gw, gemv_ws(g, gemv_cfg(t, acc, g, f.p, f.ld, f.p), false, nullptr));
     *bytes = best + gw;
     return BWLA_OK;
 }
@@ -1212,20 +1296,20 @@ bwla_status bwla_workspace_size(bwla_op op, bwla_dtype t, bwla_acc acc, bwla_lay
     *bytes = 0;
     // The pack width a call ends up with depends on pointer alignment, and the
     // default grid and split depend on the pack width, so size for the larger
-    // requirement of the two widths the call could use (kFakes).  The size
+    // requirement over what the call could use (kFakes).  The size
     // also serves the other accumulation mode, whose table entry may differ,
     // so a buffer sized once serves both.
     size_t best = 0;
     for (int a = 0; a < kAccs; ++a) {
-        for (const void *fake : kFakes) {
+        for (const Fake &f : kFakes) {
             switch (op) {
             case BWLA_OP_DOT: // dot, nrm2, asum (any increments) and the CG update share one sizing
             case BWLA_OP_NRM2:
             case BWLA_OP_CG:
                 best = std::max(best, ws_strided(n));
-                best = std::max(best, ws_dot(resolve_vector(BWLA_OP_DOT, t, a, n, {fake}, 2)));
-                best = std::max(best, ws_dot(resolve_vector(BWLA_OP_NRM2, t, a, n, {fake}, 1)));
-                best = std::max(best, ws_dot(resolve_vector(kOpCg, t, a, n, {fake}, 6)));
+                best = std::max(best, ws_dot(resolve_vector(BWLA_OP_DOT, t, a, n, {f.p}, 2)));
+                best = std::max(best, ws_dot(resolve_vector(BWLA_OP_NRM2, t, a, n, {f.p}, 1)));
+                best = std::max(best, ws_dot(resolve_vector(kOpCg, t, a, n, {f.p}, 6)));
                 break;
             case BWLA_OP_GEMV_ROWS:
             case BWLA_OP_GEMV_COLS: {
@@ -1235,9 +1319,9 @@ bwla_status bwla_workspace_size(bwla_op op, bwla_dtype t, bwla_acc acc, bwla_lay
                 if (g.out_len == 0 || g.in_len == 0)
                     break; // no kernel runs
                 if (g.rows)
-                    best = std::max(best, ws_rows(resolve_rows(t, a, g.L, g.K, fake, fake), g.L));
+                    best = std::max(best, ws_rows(resolve_rows(t, a, g.L, g.K, f.p, f.p), g.L));
                 else
-                    best = std::max(best, ws_cols(resolve_cols(t, a, g.L, g.K, fake), g.K));
+                    best = std::max(best, ws_cols(resolve_cols(t, a, g.L, g.K, f.p, f.ld), g.K));
                 break;
             }
             default:
@@ -1295,7 +1379,7 @@ bwla_status bwla_get_config(bwla_op op, bwla_dtype t, bwla_acc acc, int64_t m, i
     case BWLA_OP_NRM2: c = resolve_vector(op, t, acc, n, {}, 1); break;
     case BWLA_OP_CG: c = resolve_vector(op, t, acc, n, {}, 6); break;
     case BWLA_OP_GEMV_ROWS: c = resolve_rows(t, acc, m, n, nullptr, nullptr); break;
-    case BWLA_OP_GEMV_COLS: c = resolve_cols(t, acc, m, n, nullptr); break;
+    case BWLA_OP_GEMV_COLS: c = resolve_cols(t, acc, m, n, nullptr, 0); break;
     case BWLA_OP_GER: c = resolve_ger(t, m, n, nullptr, nullptr); break;
     case BWLA_OP_BATCH: c = resolve_batch(t, acc, (double)n); break;
     default: return fail(BWLA_ERR_INVALID_ARG, "op %d", op);

@@ -293,6 +293,7 @@ constexpr int kDppXor1 = 0xB1;       // quad_perm [1,0,3,2]
 constexpr int kDppXor2 = 0x4E;       // quad_perm [2,3,0,1]
 constexpr int kDppHalfMirror = 0x141; // lane i <-> 7-i within 8 lanes
 constexpr int kDppMirror = 0x140;     // lane i <-> 15-i within 16 lanes
+constexpr int kDppXor8 = 0x128;       // row_ror 8: lane i <-> i^8 within 16 lanes
 
 template <int CTRL> __device__ __forceinline__ DD dpp_dd(DD v)
 {
@@ -318,6 +319,32 @@ template <bool COMP> __device__ __forceinline__ DD wave_sum(DD v)
     v = combine<COMP>(v, shfl_xor_dd(v, 16));
     v = combine<COMP>(v, shfl_xor_dd(v, 32));
     return v;
+}
+
+// The halves (M = 32) or the odd and even 16-lane rows (M = 16) of two values
+// exchanged and added: lanes with bit M clear end with a summed over the lane
+// pair, the others with b.  One gfx950 lane swap per 32-bit word and no LDS.
+template <int M> __device__ __forceinline__ void swap_lanes(uint32_t &a, uint32_t &b)
+{
+    const auto r = M == 32 ? __builtin_amdgcn_permlane32_swap(a, b, false, false)
+                           : __builtin_amdgcn_permlane16_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
+}
+template <int M> __device__ __forceinline__ void swap_lanes(double &a, double &b)
+{
+    uint2 x = __builtin_bit_cast(uint2, a), y = __builtin_bit_cast(uint2, b);
+    swap_lanes<M>(x.x, y.x);
+    swap_lanes<M>(x.y, y.y);
+    a = __builtin_bit_cast(double, x);
+    b = __builtin_bit_cast(double, y);
+}
+template <bool COMP, int M> __device__ __forceinline__ DD pair_sum(DD a, DD b)
+{
+    swap_lanes<M>(a.hi, b.hi);
+    if constexpr (COMP)
+        swap_lanes<M>(a.lo, b.lo);
+    return combine<COMP>(a, b);
 }
 
 // Sum over one work-group (blockDim.x a multiple of 64, at most 1024).  `lds`

@@ -16,7 +16,9 @@
 //   1 each slice writes float64 partials and a second kernel combines them in
 //   slice order.
 //
-// cols kernel: out[k] = sum_l A[l*ld + k] v[l].  A work-group owns a tile of
+// cols kernels: out[k] = sum_l A[l*ld + k] v[l], with one line per wave access
+//   (k_gemv_cols) or several (k_gemv_cols_grouped, below; the default).  With
+//   one, a work-group owns a tile of
 //   64*V consecutive outputs (V per lane, so each wave access is 64*V
 //   contiguous elements) and one of `split` slices of the lines; its waves
 //   take interleaved lines of the slice, U lines in flight (up to 32).  Each
@@ -274,33 +276,192 @@ __global__ __launch_bounds__(1024) void k_gemv_cols(int64_t L, int64_t K, const 
     }
 }
 
+// ---------------------------------------------------------------------------
+// cols kernel with P lines per wave access: the 64 lanes are P groups of G =
+// 64 / P, each lane loads a 16-byte pack, so an access covers G * V
+// consecutive outputs (128 to 512 bytes) of P lines, and a group's U lines are
+// consecutive, so that v is one pack per trip.
+//
+// Bound by the bytes of A in flight over all CUs.  One line per access needs
+// 8-byte or narrower lanes to keep the tile at 64 columns, and with wider
+// lanes its tiles are too few to fill the chip without deep splitting.  Groups
+// give 16-byte lanes and 16- to 128-column tiles at once: a wave moves 1 KiB
+// per load, 4096 columns make 64 to 128 tiles instead of 16 to 32, and small
+// matrices need no split and no second kernel.  Before -> after, GPU time:
+// 300 x 300 f32 6.8 -> 3.2 us, 1200 x 1501 f32 11.2 -> 6.7, 16000 x 100 f32 17.7 -> 7.6
+// (with the wider line combine), 3001 x 4099 compensated bf16 30.7 -> 12.3, 16384 x
+// 20001 bf16 229 -> 112; from 64 MiB on with aligned lines both are at the rate of
+// HBM (f32 16384 x 2048 29.0 -> 27.9, 4096 x 4096 16.2 -> 16.4).
+//
+// The groups of a wave are summed by lane swaps that halve the values each
+// time (V / 2 + V / 4 exchanges, no LDS; a butterfly of every value took as
+// many vector instructions as a small matrix's products), the waves through
+// LDS with one thread per output.
+// ---------------------------------------------------------------------------
+template <typename T, int P, int U, bool COMP>
+__global__ __launch_bounds__(1024) void k_gemv_cols_grouped(int64_t L, int64_t K, const T *A, int64_t ld,
+                                                            const T *v, DD *partials, void *out, int out_f64,
+                                                            int split, const T *w, DD *dparts)
+{
+    using C = compute_t<T>;
+    using Part = std::conditional_t<COMP, DD, double>;
+    constexpr bool EXACT = std::is_same<T, bf16_t>::value;
+    constexpr int V = 16 / (int)sizeof(T), G = 64 / P, TK = G * V;
+    const int64_t blk = xcd_block();
+    const int64_t tile = blk / split;
+    const int s = (int)(blk - tile * split);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    const int gl = lane % G;
+    const int64_t k0 = tile * TK + gl * V;
+    // the last lane's pack is the last whole one of the lines (its columns
+    // from k0 on are kept), and lanes past the end repeat it
+    const int64_t kb = k0 + V <= K ? k0 : K - V;
+    const int64_t per = (L + split - 1) / split;
+    const int64_t lb = (int64_t)s * per;
+    const int64_t tn = lb + per < L ? per : (lb < L ? L - lb : 0);
+
+    Acc<C, COMP> acc[V];
+    const T *vt = v + lb;
+    const T *base = A + lb * ld + kb;
+    const int64_t step = (int64_t)nw * (P * U);
+    int64_t j = (int64_t)(wave * P + lane / G) * U; // this group's U lines of the trip
+    int64_t done = 0;
+    for (; done + step <= tn; done += step, j += step) {
+        Pack<T, V> a[U];
+        const Pack<T, U> xv = load_pack<T, U>(vt + j);
+        const T *row = base + j * ld;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            a[u] = load_pack_nt<T, V>(row + u * ld);
+        end_of_loads();
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int e = 0; e < V; ++e)
+                acc[e].template add_prod<EXACT>(widen(a[u].v[e]), widen(xv.v[u]));
+    }
+    if (j < tn) { // the last trip: lines past the end re-read the last one and are not added
+        Pack<T, V> a[U];
+        T xv[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t l = j + u < tn ? j + u : tn - 1;
+            xv[u] = vt[l];
+            a[u] = load_pack_nt<T, V>(base + l * ld);
+        }
+        end_of_loads();
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (j + u < tn)
+#pragma unroll
+                for (int e = 0; e < V; ++e)
+                    acc[e].template add_prod<EXACT>(widen(a[u].v[e]), widen(xv[u]));
+    }
+
+    // Sum the P groups of the wave: each exchange of halves leaves a lane with
+    // half of its values, summed over twice the lines.
+    DD d[V];
+#pragma unroll
+    for (int e = 0; e < V; ++e)
+        d[e] = acc[e].to_dd();
+    constexpr int R1 = V / 2, R2 = P >= 4 && V >= 4 ? V / 4 : R1; // values left per lane
+    int e0 = lane & 32 ? R1 : 0;                                  // the first of them
+#pragma unroll
+    for (int e = 0; e < R1; ++e)
+        d[e] = pair_sum<COMP, 32>(d[e], d[e + R1]);
+    if constexpr (P >= 4) {
+        if constexpr (V >= 4) {
+            e0 += lane & 16 ? R2 : 0;
+#pragma unroll
+            for (int e = 0; e < R2; ++e)
+                d[e] = pair_sum<COMP, 16>(d[e], d[e + R2]);
+        } else {
+            d[0] = pair_sum<COMP, 16>(d[0], d[0]);
+        }
+    }
+    if constexpr (P >= 8) {
+#pragma unroll
+        for (int e = 0; e < R2; ++e)
+            d[e] = combine<COMP>(d[e], dpp_dd<kDppXor8>(d[e]));
+    }
+
+    // Sum the waves in wave order through LDS, one thread per output.
+    extern __shared__ __attribute__((aligned(16))) char grouped_lds[];
+    Part *red = reinterpret_cast<Part *>(grouped_lds);
+    // (where a step above left both lanes of a pair with the same value, one writes)
+    if (!(P >= 8 && (lane & 8)) && !(P >= 4 && V == 2 && (lane & 16))) {
+#pragma unroll
+        for (int e = 0; e < R2; ++e) {
+            if constexpr (COMP)
+                red[wave * TK + gl * V + e0 + e] = d[e];
+            else
+                red[wave * TK + gl * V + e0 + e] = d[e].hi;
+        }
+    }
+    __syncthreads();
+    DD dot = {0.0, 0.0};
+    for (int t = threadIdx.x; t < TK; t += blockDim.x) {
+        DD r = {0.0, 0.0};
+        for (int wv = 0; wv < nw; ++wv) {
+            DD x = {0.0, 0.0};
+            if constexpr (COMP)
+                x = red[wv * TK + t];
+            else
+                x.hi = red[wv * TK + t];
+            r = wv == 0 ? x : combine<COMP>(r, x);
+        }
+        // slot t holds column kb + e of its pack
+        const int64_t q0 = tile * TK + (t / V) * V;
+        const int64_t k = (q0 + V <= K ? q0 : K - V) + t % V;
+        if (k < q0 || q0 >= K)
+            continue;
+        const double y = r.hi + r.lo;
+        if (split == 1) {
+            store_out(out, k, out_f64, y);
+            if (w != nullptr)
+                dot = combine<COMP>(dot, epilogue_term<C, COMP>(widen(w[k]), (C)y));
+        } else {
+            partials[(tile * split + s) * TK + (k - tile * TK)] = r;
+        }
+    }
+    if (w != nullptr && split == 1) {
+        __shared__ DD lds[16];
+        dot = block_sum<COMP>(dot, lds);
+        if (threadIdx.x == 0)
+            dparts[tile] = dot;
+    }
+}
+
 #if BWLA_T_IS_F64 // type-independent kernels live in the f64 object only
-// Second stage of a split GEMV: one thread per output sums its slices' float64
-// partials in slice order.  Consecutive outputs read consecutive partials.
-// With w (same element type as out), the work-group also reduces w_o * y_o
-// over its outputs into dparts[blockIdx.x].
-// B partials in flight per round trip: the smallest power of two (2 to 16)
-// that holds the split, so a split of up to 16 is one round trip.
-template <bool COMP, int B>
+// Second stage of a split GEMV: S threads per output, each summing a run of
+// consecutive slices' float64 partials in slice order, then the S runs in
+// order through LDS.  Consecutive threads take consecutive outputs, so they
+// read consecutive partials.  With w (same element type as out), the
+// work-group also reduces w_o * y_o over its outputs into dparts[blockIdx.x].
+// B partials in flight per round trip: the smallest power of two (2 to 8)
+// that holds a thread's run.
+template <bool COMP, int B, int S>
 __global__ __launch_bounds__(256) void k_combine_lines(const DD *partials, int64_t outputs, int64_t G,
                                                        int64_t split, void *out, int out_f64,
                                                        const void *w, DD *dparts)
 {
-    __shared__ DD lds[16];
-    const int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    constexpr int O = 256 / S; // outputs of the work-group
+    __shared__ DD lds[S > 1 ? 256 : 16];
+    const int run = threadIdx.x / O;
+    const int64_t o = (int64_t)blockIdx.x * O + threadIdx.x % O;
     const bool live = o < outputs;
-    double y = 0.0;
+    DD t = {0.0, 0.0};
     if (live) {
+        const int64_t per = S > 1 ? (split + S - 1) / S : split;
+        const int64_t q0 = run * per, q1 = q0 + per < split ? q0 + per : split;
         const int64_t g = o / G, r = o - g * G;
         const DD *p = partials + g * split * G + r;
-        // slice order as written, B partials in flight at a time: a split of
-        // s costs ceil(s / B) load round trips (one at a time, a split of 128
-        // cost 32 us of load latency).  The last batch re-reads the last
-        // partial in its unused places (no branch between the loads) and
-        // adds only the first nb.
-        DD t = {0.0, 0.0};
-        for (int64_t q = 0; q < split; q += B) {
-            const int64_t nb = split - q < B ? split - q : B;
+        // slice order as written, B partials in flight at a time: one at a
+        // time, a split of 128 cost 32 us of load latency.  The last batch
+        // re-reads the last partial in its unused places (no branch between
+        // the loads) and adds only the first nb.
+        for (int64_t q = q0; q < q1; q += B) {
+            const int64_t nb = q1 - q < B ? q1 - q : B;
             DD v[B];
 #pragma unroll
             for (int b = 0; b < B; ++b)
@@ -309,20 +470,34 @@ __global__ __launch_bounds__(256) void k_combine_lines(const DD *partials, int64
 #pragma unroll
             for (int b = 0; b < B; ++b)
                 if (b < nb)
-                    t = q + b == 0 ? v[0] : combine<COMP>(t, v[b]);
+                    t = q + b == q0 ? v[0] : combine<COMP>(t, v[b]);
         }
+    }
+    if constexpr (S > 1) {
+        lds[threadIdx.x] = t;
+        __syncthreads();
+        if (run == 0)
+#pragma unroll
+            for (int k = 1; k < S; ++k) // a run past the last slice holds zero
+                t = combine<COMP>(t, lds[k * O + threadIdx.x]);
+    }
+    double y = 0.0;
+    const bool store = live && run == 0;
+    if (store) {
         y = t.hi + t.lo;
         store_out(out, o, out_f64, y);
     }
     if (w == nullptr)
         return;
     DD d = {0.0, 0.0};
-    if (live) {
+    if (store) {
         if (out_f64)
             d = epilogue_term<double, COMP>(reinterpret_cast<const double *>(w)[o], y);
         else
             d = epilogue_term<float, COMP>(reinterpret_cast<const float *>(w)[o], (float)y);
     }
+    if constexpr (S > 1)
+        __syncthreads(); // lds is reused
     d = block_sum<COMP>(d, lds);
     if (threadIdx.x == 0)
         dparts[blockIdx.x] = d;
@@ -332,20 +507,21 @@ hipError_t launch_combine_lines(const void *partials, int64_t outputs, int64_t G
                                 bool comp, int out_f64, void *out, const void *w, void *dparts,
                                 hipStream_t s)
 {
-    const int64_t blocks = (outputs + 255) / 256;
+    const int64_t blocks = (outputs + combine_lines_outputs(split) - 1) / combine_lines_outputs(split);
     return with_bool(comp, [&](auto CP) {
-        auto go = [&](auto B) {
-            hipLaunchKernelGGL((k_combine_lines<CP.value, B.value>), dim3((unsigned)blocks), dim3(256), 0, s,
+        auto go = [&](auto B, auto S) {
+            hipLaunchKernelGGL((k_combine_lines<CP.value, B.value, S.value>), dim3((unsigned)blocks), dim3(256), 0, s,
                                (const DD *)partials, outputs, G, split, out, out_f64, w, (DD *)dparts);
             return hipGetLastError();
         };
+        constexpr std::integral_constant<int, 1> one{};
         if (split <= 2)
-            return go(std::integral_constant<int, 2>{});
+            return go(std::integral_constant<int, 2>{}, one);
         if (split <= 4)
-            return go(std::integral_constant<int, 4>{});
-        if (split <= 8)
-            return go(std::integral_constant<int, 8>{});
-        return go(std::integral_constant<int, 16>{});
+            return go(std::integral_constant<int, 4>{}, one);
+        if (split <= kCombineOne)
+            return go(std::integral_constant<int, 8>{}, one);
+        return go(std::integral_constant<int, 8>{}, std::integral_constant<int, kCombineRuns>{});
     });
 }
 #endif
@@ -386,6 +562,31 @@ hipError_t launch_gemv_rows(int64_t L, int64_t K, bool comp, const void *A, int6
 }
 
 template <typename T>
+hipError_t launch_cols_grouped(int64_t L, int64_t K, bool comp, const T *A, int64_t ld, const T *v, DD *partials,
+                               void *out, int out_f64, const Cfg &c, hipStream_t s, const T *w, DD *dparts)
+{
+    const int64_t tiles = (K + cols_tile(c) - 1) / cols_tile(c);
+    const size_t lds = (size_t)(c.block / 64) * cols_tile(c) * (comp ? sizeof(DD) : sizeof(double));
+    return with_bool(comp, [&](auto CP) {
+        return with_rows(c.rows, [&](auto P) -> hipError_t {
+            if constexpr (P.value == 1) {
+                return hipErrorInvalidValue; // one line per access: the other kernel
+            } else {
+                auto go = [&](auto U) {
+                    hipLaunchKernelGGL((k_gemv_cols_grouped<T, P.value, U.value, CP.value>),
+                                       dim3((unsigned)(tiles * c.split)), dim3(c.block), (unsigned)lds, s, L, K, A,
+                                       ld, v, partials, out, out_f64, c.split, w, dparts);
+                    return hipGetLastError();
+                };
+                if (c.unroll >= 8)
+                    return go(std::integral_constant<int, 8>{});
+                return go(std::integral_constant<int, 4>{});
+            }
+        });
+    });
+}
+
+template <typename T>
 hipError_t launch_gemv_cols(int64_t L, int64_t K, bool comp, const void *A, int64_t ld,
                             const void *v, int out_f64, void *out, void *ws, const Cfg &c,
                             hipStream_t s, const void *w, size_t dparts_offset, int dot_f64,
@@ -403,7 +604,9 @@ hipError_t launch_gemv_cols(int64_t L, int64_t K, bool comp, const void *A, int6
         }
         return with_unroll(u, f);
     };
-    hipError_t e = with_vec(c.vec, [&](auto V) {
+    hipError_t e = c.rows > 1 ? launch_cols_grouped<T>(L, K, comp, (const T *)A, ld, (const T *)v, partials, out,
+                                                       out_f64, c, s, (const T *)w, dparts)
+                              : with_vec(c.vec, [&](auto V) {
         return with_unroll_cols(c.unroll, [&](auto U) -> hipError_t {
             if constexpr (U.value > 8 && (size_t)U.value * V.value * sizeof(T) > kColsLoadBytes) {
                 return hipErrorInvalidValue;
@@ -425,8 +628,7 @@ hipError_t launch_gemv_cols(int64_t L, int64_t K, bool comp, const void *A, int6
         });
     });
     if (e == hipSuccess && c.split > 1)
-        e = launch_combine_lines(partials, K, 64 * (int64_t)c.vec, c.split, comp, out_f64, out, w,
-                                 dparts, s);
+        e = launch_combine_lines(partials, K, cols_tile(c), c.split, comp, out_f64, out, w, dparts, s);
     if (e != hipSuccess || !w)
         return e;
     return launch_combine_scalar(dparts, gemv_dot_parts(false, L, K, c), comp, false, dot_f64, dot, s);

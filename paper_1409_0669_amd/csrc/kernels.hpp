@@ -114,6 +114,12 @@ hipError_t launch_gemv_cols(int64_t L, int64_t K, bool comp, const void *A, int6
                             const void *v, int out_f64, void *out, void *ws, const Cfg &c,
                             hipStream_t s, const void *w = nullptr, size_t dparts_offset = 0,
                             int dot_f64 = 1, void *dot = nullptr);
+// The line combine's work-groups: 256 outputs for a split of up to kCombineOne
+// (one thread each), else kCombineRuns threads per output.
+constexpr int kCombineOne = 8, kCombineRuns = 8;
+inline int64_t combine_lines_outputs(int64_t split) { return split <= kCombineOne ? 256 : 256 / kCombineRuns; }
+// Outputs of one work-group of the cols kernel (c.rows: lines per wave access).
+inline int64_t cols_tile(const Cfg &c) { return (int64_t)(64 / c.rows) * c.vec; }
 // Number of float64 pairs the dot epilogue writes: one per work-group of the
 // kernel that stores y (the rows or cols kernel, or the line combine when
 // split > 1).
@@ -121,8 +127,8 @@ inline int64_t gemv_dot_parts(bool rows, int64_t L, int64_t K, const Cfg &c)
 {
     const int64_t outputs = rows ? L : K;
     if (c.split > 1)
-        return (outputs + 255) / 256;
-    return rows ? (L + c.rows - 1) / c.rows : (K + 64 * (int64_t)c.vec - 1) / (64 * (int64_t)c.vec);
+        return (outputs + combine_lines_outputs(c.split) - 1) / combine_lines_outputs(c.split);
+    return rows ? (L + c.rows - 1) / c.rows : (K + cols_tile(c) - 1) / cols_tile(c);
 }
 // --- rank-1 overwrite: A[l*ld + k] = a[l] * b[k] ---------------------------
 template <typename T>

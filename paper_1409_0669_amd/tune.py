@@ -358,22 +358,34 @@ def _rows_candidates(dtype, quick, cus=256):
             for r in (1, 2, 4, 8) for u in (1, 2) for g in GEMV_GROUPS_PER_CU]
 
 
+FIXED_GAIN = 0.93  # the rule's rate against a fixed entry's from which the rule stays
+
+
 def _cols_candidates(dtype, quick, cus=256):
-    # one element per lane included: with few outputs the cols kernel's
-    # split (and its second kernel) grows with the pack width
-    # 16 and 32 lines in flight only where the library takes them (at most 128
-    # bytes of A per lane in flight)
     es = torch.tensor([], dtype=dtype).element_size()
     native = 16 // es
     vecs = (native,) if quick else tuple(sorted({1, max(1, native // 2), native}))
-    return [dict(block=b, vec=v, unroll=u, split=0, grid=g * cus) for b in (256, 512, 1024) for v in vecs
-            for u in (2, 4, 8, 16, 32) if u <= 8 or u * v * es <= 128 for g in GEMV_GROUPS_PER_CU]
+    # the library's own rule, which follows each matrix's shape (an entry that
+    # names neither block, unroll, grid, rows nor split)
+    rule = [dict(block=0, vec=native, unroll=0, split=0, grid=0, rows=0)]
+    # several lines per wave access, 16-byte packs
+    grouped = [dict(block=b, vec=native, unroll=u, split=0, grid=g * cus, rows=r) for b in (256, 512) for u in (4, 8)
+               for r in (2, 4, 8) for g in GEMV_GROUPS_PER_CU]
+    # one line per access; one element per lane included: with few outputs
+    # the split (and the second kernel) grows with the pack width.  16 and 32
+    # lines in flight only where the library takes them (at most 128 bytes of
+    # A per lane in flight)
+    return rule + grouped + [dict(block=b, vec=v, unroll=u, split=0, grid=g * cus, rows=1) for b in (512, 1024)
+                             for v in vecs for u in (4, 8, 16) if u <= 8 or u * v * es <= 128
+                             for g in GEMV_GROUPS_PER_CU]
 
 
 # GEMV shapes tuned; each size class is tuned on every shape that falls in it
 # (the square matrices of the paper-scale workload and the tall and wide
-# shards of the differentiation workload)
-GEMV_SHAPES = ((1024, 1024), (4096, 4096), (16384, 2048), (2048, 16384), (8192, 8192), (16384, 16384))
+# shards of the differentiation workload, and odd, narrow and wide ones, so that
+# an entry is not the best of its class's squares alone)
+GEMV_SHAPES = ((1024, 1024), (4096, 4096), (16384, 2048), (2048, 16384), (8192, 8192), (16384, 16384),
+               (1501, 1200), (100, 16000), (16000, 100), (2048, 2048), (8003, 8001), (12001, 8000), (20001, 16384))
 
 
 def multi_shape_pick(workloads, candidates, reps=6, refine=6, refine_rounds=5, log=None):
@@ -530,6 +542,11 @@ def _tune_all(dtypes, quick, log, ops_, vec_sizes, gemv_shapes, ger_shapes, max_
                     ws = [Workload("gemv", dt, n=n, m=m, layout=layout, acc=acc) for (m, n) in shapes]
                     default = [w.bytes / (time_ms(w.run, reps=10) * 1e-3) / 1e9 for w in ws]
                     cfg, score, rates = multi_shape_pick(ws, cands_g, refine=refine)
+                    if layout == "col" and statistics.geometric_mean(default) >= FIXED_GAIN * score:
+                        # the library's rule (the default here) stays unless one fixed entry is
+                        # clearly better: it follows shapes that were not tuned on, and
+                        # saves launches that this GPU-time measure does not see
+                        cfg, score, rates = cands_g[0], statistics.geometric_mean(default), dict(enumerate(default))
                     entries.append((ws[0].table_op, dt, acc, cls, cfg))
                     rec = {"op": "gemv_" + layout, "dtype": dn, "acc": acc, "class": cls, "shapes": shapes,
                            "best": cfg, "best_gbs_per_shape": [round(rates[i], 1) for i in range(len(ws))],
