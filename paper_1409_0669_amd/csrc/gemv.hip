@@ -39,6 +39,32 @@
 
 namespace bwla {
 
+// The prior value of output i (read only when it is updated), and the store
+// of result v in its place.  Kernels fetch the prior value before their main
+// loop, where its latency is hidden.
+__device__ __forceinline__ double out_prior(const GemvOut &o, int64_t i)
+{
+    if (o.mode != kOutUpdate)
+        return 0.0;
+    return o.f64 ? reinterpret_cast<const double *>(o.y)[i * o.inc]
+                 : (double)reinterpret_cast<const float *>(o.y)[i * o.inc];
+}
+template <typename O> __device__ __forceinline__ O out_value(const GemvOut &o, O s, O prior)
+{
+    if (o.mode == kOutScale)
+        return (O)o.a * s;
+    if (o.mode == kOutUpdate)
+        return fma_c((O)o.a, s, (O)o.b * prior);
+    return s;
+}
+__device__ __forceinline__ void out_put(const GemvOut &o, int64_t i, double v, double prior)
+{
+    if (o.f64)
+        reinterpret_cast<double *>(o.y)[i * o.inc] = out_value<double>(o, v, prior);
+    else
+        reinterpret_cast<float *>(o.y)[i * o.inc] = out_value<float>(o, (float)v, (float)prior);
+}
+
 // One product of the dot epilogue, left as a float64 pair.
 template <typename C, bool COMP> __device__ __forceinline__ DD epilogue_term(C w, C y)
 {
@@ -49,7 +75,7 @@ template <typename C, bool COMP> __device__ __forceinline__ DD epilogue_term(C w
 
 template <typename T, int V, int R, int U, bool COMP>
 __global__ __launch_bounds__(1024) void k_gemv_rows(int64_t L, int64_t K, const T *A, int64_t ld,
-                                                    const T *v, DD *partials, void *out, int out_f64,
+                                                    const T *v, DD *partials, GemvOut out,
                                                     int split, const T *w, DD *dparts)
 {
     using C = compute_t<T>;
@@ -68,12 +94,16 @@ __global__ __launch_bounds__(1024) void k_gemv_rows(int64_t L, int64_t K, const 
     const int64_t per = (kpack + split - 1) / split;
     const int64_t pb = (int64_t)s * per;
     const int64_t pe = pb + per < kpack ? pb + per : kpack;
-    // the dot epilogue's weight of this thread's line, fetched before the
-    // main loop: read at the end it would be one more memory latency in
-    // every work-group's tail
+    // the dot epilogue's weight and the prior output of this thread's line,
+    // fetched before the main loop: read at the end they would be one more
+    // memory latency in every work-group's tail
     C wl = C(0);
-    if (w != nullptr && split == 1 && (int)threadIdx.x < nr)
-        wl = widen(w[l0 + threadIdx.x]);
+    double prior = 0.0;
+    if (split == 1 && (int)threadIdx.x < nr) {
+        if (w != nullptr)
+            wl = widen(w[l0 + threadIdx.x]);
+        prior = out_prior(out, l0 + threadIdx.x);
+    }
 
     // U trips of the pack loop per iteration, all loads first: R * U packs of
     // A in flight per thread.  Each row's sum still takes the packs in the
@@ -135,7 +165,7 @@ __global__ __launch_bounds__(1024) void k_gemv_rows(int64_t L, int64_t K, const 
             t = combine<COMP>(t, lds[wv * R + threadIdx.x]);
         if (split == 1) {
             if ((int)threadIdx.x < nr)
-                store_out(out, l0 + threadIdx.x, out_f64, t.hi + t.lo);
+                out_put(out, l0 + threadIdx.x, t.hi + t.lo, prior);
         } else {
             partials[(group * split + s) * R + threadIdx.x] = t;
         }
@@ -152,8 +182,8 @@ __global__ __launch_bounds__(1024) void k_gemv_rows(int64_t L, int64_t K, const 
 
 template <typename T, int V, int U, bool COMP>
 __global__ __launch_bounds__(1024) void k_gemv_cols(int64_t L, int64_t K, const T *A, int64_t ld,
-                                                    const T *__restrict__ v, DD *partials, void *out,
-                                                    int out_f64, int split, const T *w, DD *dparts, int xchg)
+                                                    const T *__restrict__ v, int64_t incv, DD *partials,
+                                                    GemvOut out, int split, const T *w, DD *dparts, int xchg)
 {
     using C = compute_t<T>;
     constexpr bool EXACT = std::is_same<T, bf16_t>::value;
@@ -181,36 +211,36 @@ __global__ __launch_bounds__(1024) void k_gemv_cols(int64_t L, int64_t K, const 
 
     // v[l] is read with the U lines' loads (no staging pass and no barrier
     // before the first loads of A).
-    const T *vt = v + lb;
+    const T *vt = v + lb * incv;
     const T *base = A + lb * ld + kb;
     const int64_t tn = le - lb;
     int64_t j = wave;
     if (k0 < K && kb >= 0) {
         for (; j + (int64_t)(U - 1) * nw < tn; j += (int64_t)U * nw) {
             Pack<T, V> a[U];
-            C xv[U];
+            T xv[U]; // widened after the loads: a conversion among them would wait
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 a[u] = load_pack_nt<T, V>(base + (j + (int64_t)u * nw) * ld);
-                xv[u] = widen(vt[j + (int64_t)u * nw]);
+                xv[u] = vt[(j + (int64_t)u * nw) * incv];
             }
             end_of_loads();
 #pragma unroll
             for (int u = 0; u < U; ++u)
 #pragma unroll
                 for (int e = 0; e < V; ++e)
-                    acc[e].template add_prod<EXACT>(widen(a[u].v[e]), xv[u]);
+                    acc[e].template add_prod<EXACT>(widen(a[u].v[e]), widen(xv[u]));
         }
         for (; j < tn; j += nw) {
             Pack<T, V> a = load_pack_nt<T, V>(base + j * ld);
-            const C xl = widen(vt[j]);
+            const C xl = widen(vt[j * incv]);
 #pragma unroll
             for (int e = 0; e < V; ++e)
                 acc[e].template add_prod<EXACT>(widen(a.v[e]), xl);
         }
     } else if (k0 < K) { // lines shorter than a pack
         for (; j < tn; j += nw) {
-            const C xl = widen(vt[j]);
+            const C xl = widen(vt[j * incv]);
 #pragma unroll
             for (int e = 0; e < V; ++e)
                 if (kb + e >= 0)
@@ -259,7 +289,7 @@ __global__ __launch_bounds__(1024) void k_gemv_cols(int64_t L, int64_t K, const 
             if (kb + e < k0 || k0 >= K)
                 continue;
             if (split == 1)
-                store_out(out, kb + e, out_f64, d[e].hi + d[e].lo);
+                out_put(out, kb + e, d[e].hi + d[e].lo, out_prior(out, kb + e));
             else
                 partials[(tile * split + s) * TK + (kb + e - tile * TK)] = d[e];
         }
@@ -300,7 +330,7 @@ __global__ __launch_bounds__(1024) void k_gemv_cols(int64_t L, int64_t K, const 
 // ---------------------------------------------------------------------------
 template <typename T, int P, int U, bool COMP>
 __global__ __launch_bounds__(1024) void k_gemv_cols_grouped(int64_t L, int64_t K, const T *A, int64_t ld,
-                                                            const T *v, DD *partials, void *out, int out_f64,
+                                                            const T *v, int64_t incv, DD *partials, GemvOut out,
                                                             int split, const T *w, DD *dparts)
 {
     using C = compute_t<T>;
@@ -320,15 +350,31 @@ __global__ __launch_bounds__(1024) void k_gemv_cols_grouped(int64_t L, int64_t K
     const int64_t lb = (int64_t)s * per;
     const int64_t tn = lb + per < L ? per : (lb < L ? L - lb : 0);
 
+    // slot t of the tile holds column kb + e of its pack; -1: the column is
+    // another lane's, or past the end
+    auto column = [&](int t) -> int64_t {
+        const int64_t q0 = tile * TK + (t / V) * V;
+        const int64_t k = (q0 + V <= K ? q0 : K - V) + t % V;
+        return k < q0 || q0 >= K ? -1 : k;
+    };
+    const int64_t own = split == 1 && (int)threadIdx.x < TK ? column(threadIdx.x) : -1;
+    const double prior = own >= 0 ? out_prior(out, own) : 0.0;
+
     Acc<C, COMP> acc[V];
-    const T *vt = v + lb;
+    const T *vt = v + lb * incv;
     const T *base = A + lb * ld + kb;
     const int64_t step = (int64_t)nw * (P * U);
     int64_t j = (int64_t)(wave * P + lane / G) * U; // this group's U lines of the trip
     int64_t done = 0;
     for (; done + step <= tn; done += step, j += step) {
         Pack<T, V> a[U];
-        const Pack<T, U> xv = load_pack<T, U>(vt + j);
+        Pack<T, U> xv;
+        if (incv == 1)
+            xv = load_pack<T, U>(vt + j);
+        else
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                xv.v[u] = vt[(j + u) * incv];
         const T *row = base + j * ld;
 #pragma unroll
         for (int u = 0; u < U; ++u)
@@ -346,7 +392,7 @@ __global__ __launch_bounds__(1024) void k_gemv_cols_grouped(int64_t L, int64_t K
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int64_t l = j + u < tn ? j + u : tn - 1;
-            xv[u] = vt[l];
+            xv[u] = vt[l * incv];
             a[u] = load_pack_nt<T, V>(base + l * ld);
         }
         end_of_loads();
@@ -410,14 +456,12 @@ __global__ __launch_bounds__(1024) void k_gemv_cols_grouped(int64_t L, int64_t K
                 x.hi = red[wv * TK + t];
             r = wv == 0 ? x : combine<COMP>(r, x);
         }
-        // slot t holds column kb + e of its pack
-        const int64_t q0 = tile * TK + (t / V) * V;
-        const int64_t k = (q0 + V <= K ? q0 : K - V) + t % V;
-        if (k < q0 || q0 >= K)
+        const int64_t k = column(t);
+        if (k < 0)
             continue;
         const double y = r.hi + r.lo;
         if (split == 1) {
-            store_out(out, k, out_f64, y);
+            out_put(out, k, y, t == (int)threadIdx.x ? prior : out_prior(out, k));
             if (w != nullptr)
                 dot = combine<COMP>(dot, epilogue_term<C, COMP>(widen(w[k]), (C)y));
         } else {
@@ -442,8 +486,8 @@ __global__ __launch_bounds__(1024) void k_gemv_cols_grouped(int64_t L, int64_t K
 // that holds a thread's run.
 template <bool COMP, int B, int S>
 __global__ __launch_bounds__(256) void k_combine_lines(const DD *partials, int64_t outputs, int64_t G,
-                                                       int64_t split, void *out, int out_f64,
-                                                       const void *w, DD *dparts)
+                                                       int64_t split, GemvOut out, const void *w,
+                                                       DD *dparts)
 {
     constexpr int O = 256 / S; // outputs of the work-group
     __shared__ DD lds[S > 1 ? 256 : 16];
@@ -451,6 +495,7 @@ __global__ __launch_bounds__(256) void k_combine_lines(const DD *partials, int64
     const int64_t o = (int64_t)blockIdx.x * O + threadIdx.x % O;
     const bool live = o < outputs;
     DD t = {0.0, 0.0};
+    const double prior = live && run == 0 ? out_prior(out, o) : 0.0;
     if (live) {
         const int64_t per = S > 1 ? (split + S - 1) / S : split;
         const int64_t q0 = run * per, q1 = q0 + per < split ? q0 + per : split;
@@ -485,13 +530,13 @@ __global__ __launch_bounds__(256) void k_combine_lines(const DD *partials, int64
     const bool store = live && run == 0;
     if (store) {
         y = t.hi + t.lo;
-        store_out(out, o, out_f64, y);
+        out_put(out, o, y, prior);
     }
     if (w == nullptr)
         return;
     DD d = {0.0, 0.0};
     if (store) {
-        if (out_f64)
+        if (out.f64)
             d = epilogue_term<double, COMP>(reinterpret_cast<const double *>(w)[o], y);
         else
             d = epilogue_term<float, COMP>(reinterpret_cast<const float *>(w)[o], (float)y);
@@ -504,14 +549,14 @@ __global__ __launch_bounds__(256) void k_combine_lines(const DD *partials, int64
 }
 
 hipError_t launch_combine_lines(const void *partials, int64_t outputs, int64_t G, int64_t split,
-                                bool comp, int out_f64, void *out, const void *w, void *dparts,
+                                bool comp, const GemvOut &out, const void *w, void *dparts,
                                 hipStream_t s)
 {
     const int64_t blocks = (outputs + combine_lines_outputs(split) - 1) / combine_lines_outputs(split);
     return with_bool(comp, [&](auto CP) {
         auto go = [&](auto B, auto S) {
             hipLaunchKernelGGL((k_combine_lines<CP.value, B.value, S.value>), dim3((unsigned)blocks), dim3(256), 0, s,
-                               (const DD *)partials, outputs, G, split, out, out_f64, w, (DD *)dparts);
+                               (const DD *)partials, outputs, G, split, out, w, (DD *)dparts);
             return hipGetLastError();
         };
         constexpr std::integral_constant<int, 1> one{};
@@ -531,7 +576,7 @@ hipError_t launch_combine_lines(const void *partials, int64_t outputs, int64_t G
 // epilogue pairs are then summed into *dot by the scalar combine.
 template <typename T>
 hipError_t launch_gemv_rows(int64_t L, int64_t K, bool comp, const void *A, int64_t ld,
-                            const void *v, int out_f64, void *out, void *ws, const Cfg &c,
+                            const void *v, const GemvOut &out, void *ws, const Cfg &c,
                             hipStream_t s, const void *w, size_t dparts_offset, int dot_f64,
                             void *dot)
 {
@@ -544,7 +589,7 @@ hipError_t launch_gemv_rows(int64_t L, int64_t K, bool comp, const void *A, int6
                     const int64_t groups = (L + R.value - 1) / R.value;
                     hipLaunchKernelGGL((k_gemv_rows<T, V.value, R.value, U.value, CP.value>),
                                        dim3((unsigned)(groups * c.split)), dim3(c.block), 0, s, L, K,
-                                       (const T *)A, ld, (const T *)v, partials, out, out_f64, c.split,
+                                       (const T *)A, ld, (const T *)v, partials, out, c.split,
                                        (const T *)w, dparts);
                     return hipGetLastError();
                 };
@@ -555,15 +600,15 @@ hipError_t launch_gemv_rows(int64_t L, int64_t K, bool comp, const void *A, int6
         });
     });
     if (e == hipSuccess && c.split > 1)
-        e = launch_combine_lines(partials, L, c.rows, c.split, comp, out_f64, out, w, dparts, s);
+        e = launch_combine_lines(partials, L, c.rows, c.split, comp, out, w, dparts, s);
     if (e != hipSuccess || !w)
         return e;
     return launch_combine_scalar(dparts, gemv_dot_parts(true, L, K, c), comp, false, dot_f64, dot, s);
 }
 
 template <typename T>
-hipError_t launch_cols_grouped(int64_t L, int64_t K, bool comp, const T *A, int64_t ld, const T *v, DD *partials,
-                               void *out, int out_f64, const Cfg &c, hipStream_t s, const T *w, DD *dparts)
+hipError_t launch_cols_grouped(int64_t L, int64_t K, bool comp, const T *A, int64_t ld, const T *v, int64_t incv,
+                               DD *partials, const GemvOut &out, const Cfg &c, hipStream_t s, const T *w, DD *dparts)
 {
     const int64_t tiles = (K + cols_tile(c) - 1) / cols_tile(c);
     const size_t lds = (size_t)(c.block / 64) * cols_tile(c) * (comp ? sizeof(DD) : sizeof(double));
@@ -575,7 +620,7 @@ hipError_t launch_cols_grouped(int64_t L, int64_t K, bool comp, const T *A, int6
                 auto go = [&](auto U) {
                     hipLaunchKernelGGL((k_gemv_cols_grouped<T, P.value, U.value, CP.value>),
                                        dim3((unsigned)(tiles * c.split)), dim3(c.block), (unsigned)lds, s, L, K, A,
-                                       ld, v, partials, out, out_f64, c.split, w, dparts);
+                                       ld, v, incv, partials, out, c.split, w, dparts);
                     return hipGetLastError();
                 };
                 if (c.unroll >= 8)
@@ -588,7 +633,7 @@ hipError_t launch_cols_grouped(int64_t L, int64_t K, bool comp, const T *A, int6
 
 template <typename T>
 hipError_t launch_gemv_cols(int64_t L, int64_t K, bool comp, const void *A, int64_t ld,
-                            const void *v, int out_f64, void *out, void *ws, const Cfg &c,
+                            const void *v, int64_t incv, const GemvOut &out, void *ws, const Cfg &c,
                             hipStream_t s, const void *w, size_t dparts_offset, int dot_f64,
                             void *dot)
 {
@@ -604,8 +649,8 @@ hipError_t launch_gemv_cols(int64_t L, int64_t K, bool comp, const void *A, int6
         }
         return with_unroll(u, f);
     };
-    hipError_t e = c.rows > 1 ? launch_cols_grouped<T>(L, K, comp, (const T *)A, ld, (const T *)v, partials, out,
-                                                       out_f64, c, s, (const T *)w, dparts)
+    hipError_t e = c.rows > 1 ? launch_cols_grouped<T>(L, K, comp, (const T *)A, ld, (const T *)v, incv, partials,
+                                                       out, c, s, (const T *)w, dparts)
                               : with_vec(c.vec, [&](auto V) {
         return with_unroll_cols(c.unroll, [&](auto U) -> hipError_t {
             if constexpr (U.value > 8 && (size_t)U.value * V.value * sizeof(T) > kColsLoadBytes) {
@@ -620,25 +665,25 @@ hipError_t launch_gemv_cols(int64_t L, int64_t K, bool comp, const void *A, int6
                     hipLaunchKernelGGL((k_gemv_cols<T, V.value, U.value, CP.value>),
                                        dim3((unsigned)(tiles * c.split)), dim3(c.block),
                                        (unsigned)(xchg ? xbytes : 0), s, L, K, (const T *)A, ld,
-                                       (const T *)v, partials, out, out_f64, c.split, (const T *)w,
-                                       dparts, xchg);
+                                       (const T *)v, incv, partials, out, c.split, (const T *)w, dparts,
+                                       xchg);
                     return hipGetLastError();
                 });
             }
         });
     });
     if (e == hipSuccess && c.split > 1)
-        e = launch_combine_lines(partials, K, cols_tile(c), c.split, comp, out_f64, out, w, dparts, s);
+        e = launch_combine_lines(partials, K, cols_tile(c), c.split, comp, out, w, dparts, s);
     if (e != hipSuccess || !w)
         return e;
     return launch_combine_scalar(dparts, gemv_dot_parts(false, L, K, c), comp, false, dot_f64, dot, s);
 }
 
 template hipError_t launch_gemv_rows<BWLA_T>(int64_t, int64_t, bool, const void *, int64_t,
-                                             const void *, int, void *, void *, const Cfg &,
+                                             const void *, const GemvOut &, void *, const Cfg &,
                                              hipStream_t, const void *, size_t, int, void *);
 template hipError_t launch_gemv_cols<BWLA_T>(int64_t, int64_t, bool, const void *, int64_t,
-                                             const void *, int, void *, void *, const Cfg &,
+                                             const void *, int64_t, const GemvOut &, void *, const Cfg &,
                                              hipStream_t, const void *, size_t, int, void *);
 
 } // namespace bwla

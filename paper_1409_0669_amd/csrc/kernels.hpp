@@ -97,6 +97,18 @@ hipError_t launch_strided_reduce(int mode, int64_t n, bool comp, const void *x, 
                                  int64_t incy, int out_f64, void *out, void *ws, int grid, hipStream_t s);
 
 // --- matrix-vector ---------------------------------------------------------
+// Where and how a GEMV stores its results: s_i = RN(result i) in the output type
+// O, then y[i * inc] = s_i, RN(a s_i), or RN(fma(a, s_i, RN(b y[i * inc]))) with a
+// and b rounded to O.  y points at logical entry 0 (a negative increment walks
+// backwards from it).
+enum { kOutStore = 0, kOutScale = 1, kOutUpdate = 2 };
+struct GemvOut {
+    void *y;
+    int f64, mode;
+    int64_t inc;
+    double a, b;
+};
+inline GemvOut gemv_store(void *y, int f64) { return GemvOut{y, f64, kOutStore, 1, 1.0, 0.0}; }
 // A line is a contiguous run of K elements; lines are ld apart.
 //   rows kernel:  out[l] = sum_k A[l*ld + k] * v[k]     (l < L)
 //   cols kernel:  out[k] = sum_l A[l*ld + k] * v[l]     (k < K)
@@ -104,14 +116,15 @@ hipError_t launch_strided_reduce(int mode, int64_t n, bool comp, const void *x, 
 // type as out, one entry per output) the launch also writes
 // *dot = sum_o w[o] * out[o], using gemv_dot_parts() float64 pairs at byte
 // offset dparts_offset of ws.
+// The cols kernels read v[l] at v[l * incv].
 template <typename T>
 hipError_t launch_gemv_rows(int64_t L, int64_t K, bool comp, const void *A, int64_t ld,
-                            const void *v, int out_f64, void *out, void *ws, const Cfg &c,
+                            const void *v, const GemvOut &out, void *ws, const Cfg &c,
                             hipStream_t s, const void *w = nullptr, size_t dparts_offset = 0,
                             int dot_f64 = 1, void *dot = nullptr);
 template <typename T>
 hipError_t launch_gemv_cols(int64_t L, int64_t K, bool comp, const void *A, int64_t ld,
-                            const void *v, int out_f64, void *out, void *ws, const Cfg &c,
+                            const void *v, int64_t incv, const GemvOut &out, void *ws, const Cfg &c,
                             hipStream_t s, const void *w = nullptr, size_t dparts_offset = 0,
                             int dot_f64 = 1, void *dot = nullptr);
 // The line combine's work-groups: 256 outputs for a split of up to kCombineOne
@@ -147,7 +160,7 @@ hipError_t launch_combine_scalar(const void *partials, int64_t count, bool comp,
 // w != NULL, work-group b also writes dparts[b] = sum of w[o] * out[o] over
 // its 256 outputs.
 hipError_t launch_combine_lines(const void *partials, int64_t outputs, int64_t G, int64_t split,
-                                bool comp, int out_f64, void *out, const void *w, void *dparts,
+                                bool comp, const GemvOut &out, const void *w, void *dparts,
                                 hipStream_t s);
 
 // --- batched persistent kernel ----------------------------------------------
