@@ -250,12 +250,78 @@ Cfg resolve_vector(int op, int t, int acc, int64_t n, std::initializer_list<cons
     return c;
 }
 
-Cfg resolve_rows(int t, int acc, int64_t L, int64_t K, const void *A, const void *v)
+// The rows kernel's shape when the table names none, from the matrix's own
+// (GPU times of back-to-back calls on rotating matrices; "entry" is the size
+// class's fixed entry that the table held before).
+//
+// One slice per line: a split's second kernel costs more than the work-groups
+// it adds give, even for few lines (500 x 500 f64 3.3 us against 5.5 with the
+// entry's split of 3, 500 x 30000 f32 12.1 against 17.6 with 5).  Only 16384 x 16384 f64
+// keeps two (295 us against 301).
+//
+// Below 256 MiB two lines and two packs of each per thread, and as few waves
+// per line as leave 8 on each CU: 4096 x 4096 with one wave per pair of lines takes
+// f64 22.4 us, f32 13.1, compensated bf16 9.1 against the entries' 23.7,
+// 14.4 and 11.8.  One line for few lines and for the compensated forms of up to 2048
+// (500 x 500 compensated bf16 3.1 us against 3.5); four for many short lines, whose
+// work-groups are otherwise too many to dispatch (16000 x 100 f64 4.9 against 7.8).
+//
+// From 256 MiB on: 1024 threads with one pack of each of two lines where long
+// lines fill them evenly (8192 x 8192 f64 76.9 us against 78.5 at 512), else 512
+// threads; the compensated forms as few threads as take 8 packs each (16384 x 16384
+// bf16 83.8 us at 256 threads, 116 at 512; 20001 x 5000 f32 64.9 at 256, 86.8 at 512),
+// and four long f64 or bf16 lines (f64 300 us at 16384 x 16384, 303 with two; bf16 90, 97).
+// With the dot epilogue four lines always: fewer work-groups have its tail
+// (8192 x 8192 f64 80.5 us, 81.8 with two).  A line's sum does not depend on it.
+Cfg rows_rule(int t, int acc, int64_t L, int64_t K, bool with_dot)
+{
+    const bool comp = acc == BWLA_ACC_COMPENSATED;
+    const double bytes = (double)L * K * dsize(t), mib = 1 << 20;
+    Cfg c{};
+    c.vec = native_vec(t);
+    c.rows = c.unroll = 2;
+    c.split = 1;
+    const int64_t packs = std::max<int64_t>(1, K / c.vec);
+    if (bytes >= 256 * mib) {
+        if (with_dot)
+            c.rows = 4;
+        const bool even = (double)packs / (double)(ceil_div(packs, 1024) * 1024) >= 0.9;
+        c.block = 512;
+        if (comp) {
+            while (c.block > 128 && packs < 8 * c.block)
+                c.block /= 2;
+            if (t != BWLA_F32 && packs >= 2048)
+                c.rows = 4;
+        } else if (packs >= 3584 && even) {
+            c.block = 1024;
+            c.unroll = 1;
+            if (t == BWLA_F64 && packs >= 8192 && bytes >= 1024 * mib)
+                c.split = 2;
+        }
+    } else {
+        if (L < 400 || (comp && L <= 2048 && packs <= 512))
+            c.rows = 1;
+        else if (packs <= 64 && L >= 8192)
+            c.rows = 4;
+        const int64_t groups = std::max<int64_t>(1, ceil_div(L, c.rows));
+        int64_t waves = groups < 3000 ? ceil_div(2048, groups) : packs < 1500 ? 2 : 4;
+        waves = std::min<int64_t>({waves, ceil_div(packs, 64), 16});
+        c.block = (int)(64 * waves);
+        if (packs <= c.block)
+            c.unroll = 1;
+    }
+    c.grid = (int)std::min<int64_t>(ceil_div(L, c.rows) * c.split, 0x7fffffff);
+    return c;
+}
+
+Cfg resolve_rows(int t, int acc, int64_t L, int64_t K, const void *A, const void *v, bool with_dot = false)
 {
     bwla_config u = lookup(BWLA_OP_GEMV_ROWS, t, acc, (double)L * K * dsize(t));
     Cfg c;
     c.block = u.block ? u.block : 1024;
     c.vec = fit_vec(u.vec ? u.vec : native_vec(t), dsize(t), {A, v});
+    if (c.vec == native_vec(t) && !u.block && !u.unroll && !u.grid && !u.rows && !u.split)
+        return rows_rule(t, acc, L, K, with_dot);
     c.unroll = u.unroll == 2 ? 2 : 1; // packs of each line in flight per thread: 1 or 2
     c.inc = 0;
     c.rows = u.rows ? u.rows : 2;
@@ -986,9 +1052,10 @@ static size_t gemv_ws(const GemvPlan &g, const Cfg &c, bool with_dot, size_t *dp
     return base + (size_t)gemv_dot_parts(g.rows, g.L, g.K, c) * sizeof(DD);
 }
 
-static Cfg gemv_cfg(bwla_dtype t, int acc, const GemvPlan &g, const void *A, int64_t lda, const void *x)
+static Cfg gemv_cfg(bwla_dtype t, int acc, const GemvPlan &g, const void *A, int64_t lda, const void *x,
+                    bool with_dot = false)
 {
-    return g.rows ? resolve_rows(t, acc, g.L, g.K, A, x) : resolve_cols(t, acc, g.L, g.K, A, lda);
+    return g.rows ? resolve_rows(t, acc, g.L, g.K, A, x, with_dot) : resolve_cols(t, acc, g.L, g.K, A, lda);
 }
 
 // Shared body of bwla_gemv and bwla_gemv_dot (w == NULL: no epilogue).
@@ -1052,7 +1119,7 @@ static bwla_status gemv_common(bwla_dtype t, bwla_acc acc, bwla_layout layout, i
     }
     const bool comp = acc == BWLA_ACC_COMPENSATED;
     const int of64 = out_t == BWLA_F64, df64 = dot_t == BWLA_F64;
-    Cfg c = gemv_cfg(t, acc, g, A, lda, x);
+    Cfg c = gemv_cfg(t, acc, g, A, lda, x, fused);
     size_t off = 0;
     const size_t need = gemv_ws(g, c, fused, &off);
     if (need && (!ws || ws_bytes < need))
@@ -1108,7 +1175,7 @@ bwla_status bwla_gemv_dot_workspace_size(bwla_dtype t, bwla_layout layout, int t
     size_t best = 0; // largest over the pack widths and accumulation modes the call could use
     for (int acc = 0; acc < kAccs; ++acc)
         for (const Fake &f : kFakes)
-            best = std::max(best, gemv_ws(g, gemv_cfg(t, acc, g, f.p, f.ld, f.p), true, nullptr));
+            best = std::max(best, gemv_ws(g, gemv_cfg(t, acc, g, f.p, f.ld, f.p, true), true, nullptr));
     *bytes = best;
     return BWLA_OK;
 }

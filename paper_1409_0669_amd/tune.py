@@ -159,6 +159,7 @@ class Workload:
         self.table_acc = acc if op in REDUCING else None
         name = {torch.float64: "f64", torch.float32: "f32", torch.bfloat16: "bf16"}[dtype]
         s = torch.tensor([], dtype=dtype).element_size()
+        self.native = 16 // s
         if op in ("copy", "axpby", "dot", "nrm2", "cg"):
             self.y = W.device_draw(n, name, 0, 1)
             self.z = W.device_draw(n, name, 0, 2)
@@ -354,8 +355,15 @@ GEMV_GROUPS_PER_CU = (0, 1, 2, 4, 8, 16, 32, 64)
 def _rows_candidates(dtype, quick, cus=256):
     native = 16 // torch.tensor([], dtype=dtype).element_size()
     vecs = (native,) if quick else (max(1, native // 2), native)
-    return [dict(block=b, vec=v, rows=r, unroll=u, split=0, grid=g * cus) for b in (256, 512, 1024) for v in vecs
-            for r in (1, 2, 4, 8) for u in (1, 2) for g in GEMV_GROUPS_PER_CU]
+    return [_gemv_rule(native)] + [dict(block=b, vec=v, rows=r, unroll=u, split=0, grid=g * cus)
+                                   for b in (64, 128, 256, 512, 1024) for v in vecs for r in (1, 2, 4, 8)
+                                   for u in (1, 2) for g in GEMV_GROUPS_PER_CU]
+
+
+def _gemv_rule(native):
+    """The library's own rule, which follows each matrix's shape: an entry
+    that names neither block, unroll, grid, rows nor split."""
+    return dict(block=0, vec=native, unroll=0, split=0, grid=0, rows=0)
 
 
 FIXED_GAIN = 0.93  # the rule's rate against a fixed entry's from which the rule stays
@@ -365,9 +373,6 @@ def _cols_candidates(dtype, quick, cus=256):
     es = torch.tensor([], dtype=dtype).element_size()
     native = 16 // es
     vecs = (native,) if quick else tuple(sorted({1, max(1, native // 2), native}))
-    # the library's own rule, which follows each matrix's shape (an entry that
-    # names neither block, unroll, grid, rows nor split)
-    rule = [dict(block=0, vec=native, unroll=0, split=0, grid=0, rows=0)]
     # several lines per wave access, 16-byte packs
     grouped = [dict(block=b, vec=native, unroll=u, split=0, grid=g * cus, rows=r) for b in (256, 512) for u in (4, 8)
                for r in (2, 4, 8) for g in GEMV_GROUPS_PER_CU]
@@ -375,9 +380,9 @@ def _cols_candidates(dtype, quick, cus=256):
     # the split (and the second kernel) grows with the pack width.  16 and 32
     # lines in flight only where the library takes them (at most 128 bytes of
     # A per lane in flight)
-    return rule + grouped + [dict(block=b, vec=v, unroll=u, split=0, grid=g * cus, rows=1) for b in (512, 1024)
-                             for v in vecs for u in (4, 8, 16) if u <= 8 or u * v * es <= 128
-                             for g in GEMV_GROUPS_PER_CU]
+    single = [dict(block=b, vec=v, unroll=u, split=0, grid=g * cus, rows=1) for b in (512, 1024) for v in vecs
+              for u in (4, 8, 16) if u <= 8 or u * v * es <= 128 for g in GEMV_GROUPS_PER_CU]
+    return [_gemv_rule(native)] + grouped + single
 
 
 # GEMV shapes tuned; each size class is tuned on every shape that falls in it
@@ -542,11 +547,12 @@ def _tune_all(dtypes, quick, log, ops_, vec_sizes, gemv_shapes, ger_shapes, max_
                     ws = [Workload("gemv", dt, n=n, m=m, layout=layout, acc=acc) for (m, n) in shapes]
                     default = [w.bytes / (time_ms(w.run, reps=10) * 1e-3) / 1e9 for w in ws]
                     cfg, score, rates = multi_shape_pick(ws, cands_g, refine=refine)
-                    if layout == "col" and statistics.geometric_mean(default) >= FIXED_GAIN * score:
+                    if statistics.geometric_mean(default) >= FIXED_GAIN * score:
                         # the library's rule (the default here) stays unless one fixed entry is
                         # clearly better: it follows shapes that were not tuned on, and
                         # saves launches that this GPU-time measure does not see
-                        cfg, score, rates = cands_g[0], statistics.geometric_mean(default), dict(enumerate(default))
+                        cfg, rates = _gemv_rule(ws[0].native), dict(enumerate(default))
+                        score = statistics.geometric_mean(default)
                     entries.append((ws[0].table_op, dt, acc, cls, cfg))
                     rec = {"op": "gemv_" + layout, "dtype": dn, "acc": acc, "class": cls, "shapes": shapes,
                            "best": cfg, "best_gbs_per_shape": [round(rates[i], 1) for i in range(len(ws))],
