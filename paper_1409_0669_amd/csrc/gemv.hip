@@ -328,7 +328,9 @@ __global__ __launch_bounds__(1024) void k_gemv_cols(int64_t L, int64_t K, const 
 // many vector instructions as a small matrix's products), the waves through
 // LDS with one thread per output.
 // ---------------------------------------------------------------------------
-template <typename T, int P, int U, bool COMP>
+// UNIT: v has unit increment and is read in packs (a run-time choice between the
+// two inside the loop made its loads wait: 16384 x 16384 bf16 79 -> 107 us).
+template <typename T, int P, int U, bool COMP, bool UNIT>
 __global__ __launch_bounds__(1024) void k_gemv_cols_grouped(int64_t L, int64_t K, const T *A, int64_t ld,
                                                             const T *v, int64_t incv, DD *partials, GemvOut out,
                                                             int split, const T *w, DD *dparts)
@@ -361,6 +363,8 @@ __global__ __launch_bounds__(1024) void k_gemv_cols_grouped(int64_t L, int64_t K
     const double prior = own >= 0 ? out_prior(out, own) : 0.0;
 
     Acc<C, COMP> acc[V];
+    if constexpr (UNIT)
+        incv = 1;
     const T *vt = v + lb * incv;
     const T *base = A + lb * ld + kb;
     const int64_t step = (int64_t)nw * (P * U);
@@ -369,12 +373,13 @@ __global__ __launch_bounds__(1024) void k_gemv_cols_grouped(int64_t L, int64_t K
     for (; done + step <= tn; done += step, j += step) {
         Pack<T, V> a[U];
         Pack<T, U> xv;
-        if (incv == 1)
+        if constexpr (UNIT) {
             xv = load_pack<T, U>(vt + j);
-        else
+        } else {
 #pragma unroll
             for (int u = 0; u < U; ++u)
                 xv.v[u] = vt[(j + u) * incv];
+        }
         const T *row = base + j * ld;
 #pragma unroll
         for (int u = 0; u < U; ++u)
@@ -617,15 +622,17 @@ hipError_t launch_cols_grouped(int64_t L, int64_t K, bool comp, const T *A, int6
             if constexpr (P.value == 1) {
                 return hipErrorInvalidValue; // one line per access: the other kernel
             } else {
-                auto go = [&](auto U) {
-                    hipLaunchKernelGGL((k_gemv_cols_grouped<T, P.value, U.value, CP.value>),
+                auto go = [&](auto U, auto unit) {
+                    hipLaunchKernelGGL((k_gemv_cols_grouped<T, P.value, U.value, CP.value, unit.value>),
                                        dim3((unsigned)(tiles * c.split)), dim3(c.block), (unsigned)lds, s, L, K, A,
                                        ld, v, incv, partials, out, c.split, w, dparts);
                     return hipGetLastError();
                 };
+                if (incv != 1)
+                    return go(std::integral_constant<int, 4>{}, std::false_type{});
                 if (c.unroll >= 8)
-                    return go(std::integral_constant<int, 8>{});
-                return go(std::integral_constant<int, 4>{});
+                    return go(std::integral_constant<int, 8>{}, std::true_type{});
+                return go(std::integral_constant<int, 4>{}, std::true_type{});
             }
         });
     });
