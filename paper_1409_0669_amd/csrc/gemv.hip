@@ -628,11 +628,12 @@ hipError_t launch_cols_grouped(int64_t L, int64_t K, bool comp, const T *A, int6
                                        ld, v, incv, partials, out, c.split, w, dparts);
                     return hipGetLastError();
                 };
-                if (incv != 1)
-                    return go(std::integral_constant<int, 4>{}, std::false_type{});
-                if (c.unroll >= 8)
-                    return go(std::integral_constant<int, 8>{}, std::true_type{});
-                return go(std::integral_constant<int, 4>{}, std::true_type{});
+                // (the trip's lines decide the order of a sum, so x's increment may not)
+                return with_bool(incv == 1, [&](auto unit) {
+                    if (c.unroll >= 8)
+                        return go(std::integral_constant<int, 8>{}, unit);
+                    return go(std::integral_constant<int, 4>{}, unit);
+                });
             }
         });
     });
