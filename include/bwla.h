@@ -70,10 +70,11 @@ typedef enum BWLA_ENUM_INT { BWLA_ROW_MAJOR = 0, BWLA_COL_MAJOR = 1 } bwla_layou
 /* Accumulation of reductions.  PLAIN: one running sum per thread in the
  * compute precision.  COMPENSATED: the running sum carries its rounding error
  * (TwoSum) and, for f64/f32, the product error (TwoProduct by fma) -- the
- * Dot2 scheme of Ogita, Rump and Oishi; for bf16 the products are exact in
- * f32 and only the sum is compensated (Kahan-style).  In both modes, partial
- * sums leave the thread as float64 and every combine across threads and
- * work-groups is done in float64 (double-float64 pairs when COMPENSATED). */
+ * Dot2 scheme of Ogita, Rump and Oishi; for bf16 the products are exact and
+ * summed in float64 (less error than a float32 sum carrying its own, and
+ * fewer instructions on this device).  In both modes, partial sums leave the
+ * thread as float64 and every combine across threads and work-groups is done
+ * in float64 (double-float64 pairs when COMPENSATED). */
 typedef enum BWLA_ENUM_INT { BWLA_ACC_PLAIN = 0, BWLA_ACC_COMPENSATED = 1 } bwla_acc;
 
 /* Loop increment of the streaming kernels, the paper's two kernel skeletons

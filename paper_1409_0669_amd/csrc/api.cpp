@@ -368,7 +368,7 @@ Cfg resolve_rows(int t, int acc, int64_t L, int64_t K, const void *A, const void
 // One work-group count per size class, as the table held before, gave f32
 // 16000 x 100 17.8 us where this gives 7.6, and 1200 x 1501 11.3 where this gives 6.6.
 //
-// Depth: small matrices and the compensated f32 and bf16 forms (vector-ALU
+// Depth: small matrices and the compensated f32 form (vector-ALU
 // bound with 4 waves) run 512 threads with 4 lines each, the others 256 with 8.
 //
 // One line per access (k_gemv_cols) stays where it is the faster: plain f64
@@ -415,7 +415,7 @@ Cfg cols_rule(int t, int acc, int64_t L, int64_t K, bool line_aligned)
         }
         c.rows = best_rows;
         c.split = (int)best_split;
-        const bool deep = bytes >= 32.0 * (1 << 20) && (!comp || f64);
+        const bool deep = bytes >= 32.0 * (1 << 20) && (!comp || t != BWLA_F32);
         c.unroll = deep ? 8 : 4;
         c.block = deep ? 256 : 512;
     }

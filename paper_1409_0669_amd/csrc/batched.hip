@@ -41,7 +41,7 @@ __device__ __forceinline__ void gemv_tile(const BatchGemv &g, int64_t rb, int64_
         const int64_t r = base + sub;
         const int64_t rr = r < re ? r : re - 1;
         const T *row = A + rr * g.lda;
-        Acc<C, COMP> acc;
+        acc_t<T, COMP> acc;
         for (int64_t p = gl; p < kpack; p += G) {
             Pack<T, V> av = load_pack<T, V>(row + p * V), xv = load_pack<T, V>(x + p * V);
 #pragma unroll
@@ -66,7 +66,7 @@ __device__ __forceinline__ void dot_chunk(const BatchArgs &a, const BatchItem &w
     const int lane = threadIdx.x & 63;
     const BatchDot &d = a.dots[w.prob];
     const T *x = (const T *)d.x, *y = (const T *)d.y;
-    Acc<C, COMP> acc[2];
+    acc_t<T, COMP> acc[2];
     const int64_t pb = w.begin / V, pe = w.end / V; // chunk starts are pack-aligned
     int64_t p = pb + lane;
     for (; p + 64 < pe; p += 128) {
@@ -157,7 +157,7 @@ __device__ __forceinline__ void gemv_tile_block(const BatchGemv &g, int64_t rb, 
             const int64_t r = base + j * slots + sub;
             row[j] = A + (r < re ? r : re - 1) * g.lda;
         }
-        Acc<C, COMP> acc[RB];
+        acc_t<T, COMP> acc[RB];
         int64_t p = gl;
         for (; p + (int64_t)(U - 1) * G < kpack; p += (int64_t)U * G) {
             Pack<T, V> xv[U], av[RB][U];
@@ -261,7 +261,7 @@ __device__ __forceinline__ void staged_rows(const BatchGemv &g, int64_t rb, int6
         for (int e = 0; e < V; ++e)
             xo[e] = ((h + e) % V) * P + (h + e) / V + gl;
         const T *ap = row + h + (int64_t)gl * V;
-        Acc<C, COMP> acc[2];
+        acc_t<T, COMP> acc[2];
         int p = gl;
         for (; p + (U - 1) * G < np; p += U * G) {
             Pack<T, V> av[U];
@@ -378,7 +378,7 @@ __device__ __forceinline__ void dot_chunk_block(const BatchArgs &a, const BatchI
     constexpr int U = kChunkPacksInFlight;
     const BatchDot &d = a.dots[w.prob];
     const T *x = (const T *)d.x, *y = (const T *)d.y;
-    Acc<C, COMP> acc[2];
+    acc_t<T, COMP> acc[2];
     const int64_t pb = w.begin / V, pe = w.end / V; // chunk starts are pack-aligned
     const int64_t step = blockDim.x;
     int64_t p = pb + threadIdx.x;

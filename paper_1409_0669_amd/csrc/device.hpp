@@ -11,6 +11,7 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 
 namespace bwla {
 
@@ -263,6 +264,27 @@ template <typename C, bool COMP> struct Acc {
         return r;
     }
 };
+
+// Compensated accumulator of bf16 storage: a float64 sum.  The products of two
+// bf16 values are exact in float64, so one fma per term is all, and its error
+// (2^-53 per term) is below that of a float32 sum that carries its error (2^-48).
+// On gfx950 float64 fma issues at the float32 rate, so a term costs a conversion
+// and an fma where the TwoSum of the float32 form took seven adds and a product:
+// y = A x 16384 x 16384 89.7 -> 84.8 us, 3001 x 4099 9.7 -> 9.0, transposed 300 x 300 6.3 ->
+// 5.4, dot of 2^26 44.9 -> 43.8, the uneven batch's GEMV tiles 216 -> 204.
+struct AccF64 {
+    double s = 0;
+    template <bool EXACT_PROD>
+    __device__ __forceinline__ void add_prod(float a, float b)
+    {
+        s = __builtin_fma((double)a, (double)b, s);
+    }
+    __device__ __forceinline__ DD to_dd() const { return DD{s, 0.0}; }
+};
+// (The fused CG update keeps the float32 form: four streams per term, and the
+// conversions would sit between a trip's loads.)
+template <typename T, bool COMP>
+using acc_t = std::conditional_t<std::is_same_v<T, bf16_t> && COMP, AccF64, Acc<compute_t<T>, COMP>>;
 
 template <bool COMP> __device__ __forceinline__ DD combine(DD a, DD b)
 {

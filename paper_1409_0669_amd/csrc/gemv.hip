@@ -108,7 +108,7 @@ __global__ __launch_bounds__(1024) void k_gemv_rows(int64_t L, int64_t K, const 
     // U trips of the pack loop per iteration, all loads first: R * U packs of
     // A in flight per thread.  Each row's sum still takes the packs in the
     // order p, p + blockDim, ..., so U does not change any result.
-    Acc<C, COMP> acc[R];
+    acc_t<T, COMP> acc[R];
     int64_t p = pb + threadIdx.x;
     for (; p + (int64_t)(U - 1) * blockDim.x < pe; p += (int64_t)U * blockDim.x) {
         Pack<T, V> xv[U], av[U][R];
@@ -207,7 +207,7 @@ __global__ __launch_bounds__(1024) void k_gemv_cols(int64_t L, int64_t K, const 
 
     // LDS for the cross-wave combine (the hand-over path).
     __shared__ __attribute__((aligned(16))) DD red[TK];
-    Acc<C, COMP> acc[V];
+    acc_t<T, COMP> acc[V];
 
     // v[l] is read with the U lines' loads (no staging pass and no barrier
     // before the first loads of A).
@@ -362,7 +362,7 @@ __global__ __launch_bounds__(1024) void k_gemv_cols_grouped(int64_t L, int64_t K
     const int64_t own = split == 1 && (int)threadIdx.x < TK ? column(threadIdx.x) : -1;
     const double prior = own >= 0 ? out_prior(out, own) : 0.0;
 
-    Acc<C, COMP> acc[V];
+    acc_t<T, COMP> acc[V];
     if constexpr (UNIT)
         incv = 1;
     const T *vt = v + lb * incv;

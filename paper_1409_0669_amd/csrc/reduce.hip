@@ -16,8 +16,8 @@
 namespace bwla {
 
 // One term of the reduction: x_i y_i, x_i^2, or |x_i| (an exact product by 1).
-template <int MODE, bool EXACT, typename C, bool COMP>
-__device__ __forceinline__ void reduce_term(Acc<C, COMP> &acc, C a, C b)
+template <int MODE, bool EXACT, typename A, typename C>
+__device__ __forceinline__ void reduce_term(A &acc, C a, C b)
 {
     if constexpr (MODE == kRedAbs)
         acc.template add_prod<true>(abs_c(a), C(1));
@@ -31,7 +31,7 @@ __global__ __launch_bounds__(1024) void k_dot(int64_t n, const T *x, const T *y,
 {
     using C = compute_t<T>;
     constexpr bool EXACT = std::is_same<T, bf16_t>::value;
-    Acc<C, COMP> acc[U];
+    acc_t<T, COMP> acc[U];
     x += head;
     if constexpr (MODE == kRedDot)
         y += head;

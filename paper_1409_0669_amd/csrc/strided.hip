@@ -72,7 +72,7 @@ __global__ __launch_bounds__(256) void k_strided_elem(int64_t n, compute_t<T> a,
 }
 
 template <typename T, int MODE, bool COMP>
-__device__ __forceinline__ void strided_term(Acc<compute_t<T>, COMP> &acc, T xv, T yv)
+__device__ __forceinline__ void strided_term(acc_t<T, COMP> &acc, T xv, T yv)
 {
     constexpr bool EXACT = std::is_same<T, bf16_t>::value;
     const compute_t<T> a = widen(xv);
@@ -88,7 +88,7 @@ template <typename T, int MODE, int U, bool COMP>
 __global__ __launch_bounds__(256) void k_strided_reduce(int64_t n, const T *x, int64_t incx, const T *y,
                                                         int64_t incy, DD *partials, void *out, int out_f64)
 {
-    Acc<compute_t<T>, COMP> acc[U];
+    acc_t<T, COMP> acc[U];
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     int64_t i = xcd_block() * blockDim.x + threadIdx.x;
     for (; i + (U - 1) * stride < n; i += U * stride) {
