@@ -108,8 +108,8 @@ typedef enum BWLA_ENUM_INT {
  *                     rule that follows the matrix's shape
  *   GER:              block, vec, rows
  *   BATCH:            block (work-group size, at most 512), unroll (packs of a
- *                     GEMV row each lane of a staged tile owns: sets how many
- *                     lanes share a row); its size class is that of the plan's
+ *                     GEMV row each lane of a tile owns, 8 at most: sets how
+ *                     many lanes, 8 to 64, share a row of less than 4 KiB); its size class is that of the plan's
  *                     algorithmic bytes
  * block:  threads per work-group, a multiple of 64 in [64, 1024]
  * vec:    consecutive elements per thread per access: 1, 2, 4, 8 or 16 (the
@@ -321,8 +321,8 @@ bwla_status bwla_workspace_size(bwla_op op, bwla_dtype t, bwla_acc acc, bwla_lay
  * A plan holds many row-major GEMVs (y = A x, out_t output) and many dots
  * (out = <x, y>, out_t output) of one storage type.  Work is flattened into
  * items (row tiles of a GEMV, chunks of a dot) ordered largest first and run
- * with one work-group per item, one launch per kind of item (GEMV tiles with
- * x staged in LDS, the other GEMV tiles, dot chunks; the hardware dispatcher
+ * with one work-group per item, one launch per kind of item (GEMV tiles read
+ * in 16-byte packs, the other GEMV tiles, dot chunks; the hardware dispatcher
  * hands out each launch's items in order).  Each dot's chunk partials are
  * combined in chunk order by a finalize kernel, so results do not depend on
  * the batch order or on scheduling.
@@ -334,7 +334,7 @@ bwla_status bwla_workspace_size(bwla_op op, bwla_dtype t, bwla_acc acc, bwla_lay
  * replay: launches the captured graph.
  * Descriptor pointers must stay valid while the plan is used.
  * cfg (may be NULL) sets the work-group size (cfg->block, a multiple of 64
- * up to 512) and the packs of a GEMV row each lane of a staged tile owns
+ * up to 512) and the packs of a GEMV row each lane of a tile owns
  * (cfg->unroll, a power of two up to 32); other fields are ignored.  A zero
  * (or NULL) field takes the configuration table's BWLA_OP_BATCH entry for
  * (t, acc, size class of the plan's algorithmic bytes), else the defaults

@@ -1,7 +1,7 @@
 """``BatchPlan``: many uneven row-major GEMVs and dots in one batched launch --
 one work-group per work item (row tiles of the GEMVs, chunks of the dots,
-largest first), one kernel per kind of item (GEMV tiles with x staged in LDS,
-the other GEMV tiles, dot chunks), then a finalize kernel that combines each
+largest first), one kernel per kind of item (GEMV tiles read in
+16-byte packs, the other GEMV tiles, dot chunks), then a finalize kernel that combines each
 dot's chunk partials in chunk order -- optionally captured in a HIP graph and
 replayed.  The work-group size and the packs of a GEMV row each lane owns come
 from the tuning table's batch entry unless given."""
@@ -49,7 +49,7 @@ class BatchPlan:
                 raise BwlaError(L.ERR_INVALID_ARG, "dot %d: out must be one %s" % (i, self.out_dtype))
             d[i] = L.DotDesc(x.data_ptr(), y.data_ptr(), x.numel(), out.data_ptr())
         # block (work-group size) and packs (packs of a GEMV row per lane of a
-        # staged tile): 0 takes the tuning table's batch entry
+        # tile): 0 takes the tuning table's batch entry
         cfg = L.Config(block=int(block), grid=int(grid), unroll=int(packs))
         h = ctypes.c_void_p()
         with torch.cuda.device(self.device):

@@ -474,14 +474,14 @@ Cfg resolve_ger(int t, int64_t L, int64_t K, const void *b, const void *A)
 }
 
 // Batch plans: the work-group size and the packs of a GEMV row each lane of a
-// staged tile owns (in unroll), from the table entry of the plan's size class.
+// tile owns (in unroll), from the table entry of the plan's size class.
 Cfg resolve_batch(int t, int acc, double bytes)
 {
     bwla_config u = lookup(BWLA_OP_BATCH, t, acc, bytes);
     Cfg c{};
     c.block = std::min(u.block ? u.block : 256, 512);
     c.vec = native_vec(t);
-    c.unroll = u.unroll ? u.unroll : kStagedPacks;
+    c.unroll = u.unroll ? u.unroll : kRowPacks;
     c.grid = 0;
     c.inc = 0;
     c.rows = 1;
@@ -1512,8 +1512,7 @@ struct bwla_batch_plan {
     int grid = 0, block = 256, vec = 1;
     int64_t n_items = 0, n_dots = 0;
     int64_t n_gemv_items = 0; // grouped launch: GEMV items come first
-    int64_t n_staged_items = 0; // of those, the staged tiles come first
-    size_t stage_bytes = 0;     // dynamic LDS of the staged-tile kernel
+    int64_t n_packed_items = 0; // of those, the tiles read in packs come first
     double bytes = 0;
     BatchItem *d_items = nullptr;
     BatchGemv *d_gemv = nullptr;
@@ -1566,7 +1565,7 @@ hipError_t enqueue_batch(bwla_batch_plan *p, hipStream_t s)
     a.items = p->d_items;
     a.n_items = p->n_items;
     a.n_gemv_items = p->n_gemv_items;
-    a.n_staged_items = p->n_staged_items;
+    a.n_packed_items = p->n_packed_items;
     a.gemv = p->d_gemv;
     a.dots = p->d_dots;
     a.partials = p->d_partials;
@@ -1577,7 +1576,7 @@ hipError_t enqueue_batch(bwla_batch_plan *p, hipStream_t s)
         using T = std::remove_pointer_t<decltype(tag)>;
         if (p->persistent)
             return launch_batched<T>(a, p->acc == BWLA_ACC_COMPENSATED, p->grid, p->block, s);
-        return launch_grouped<T>(a, p->acc == BWLA_ACC_COMPENSATED, p->block, p->stage_bytes, s);
+        return launch_grouped<T>(a, p->acc == BWLA_ACC_COMPENSATED, p->block, s);
     });
     if (e != hipSuccess)
         return e;
@@ -1673,6 +1672,7 @@ bwla_status bwla_batch_plan_create(bwla_dtype t, bwla_acc acc, bwla_dtype out_t,
     // 64 * 16 elements, so every chunk begins on a pack boundary.
     const int64_t kTileElems = p->persistent ? (1 << 15) : (1 << 16); // elements of A per GEMV row tile
     const int64_t kChunk = p->persistent ? (1 << 14) : (1 << 16);     // elements per dot chunk
+
     for (int i = 0; i < ng; ++i) {
         const bwla_gemv_desc &q = g[i];
         BatchGemv &b = hg[i];
@@ -1682,43 +1682,39 @@ bwla_status bwla_batch_plan_create(bwla_dtype t, bwla_acc acc, bwla_dtype out_t,
         b.lda = q.lda;
         b.x = q.x;
         b.y = q.y;
-        // grouped launch: x staged in LDS when it fits (rows at any
-        // alignment; measured as fast as, or faster than, x in registers on
-        // aligned rows), else 16-byte packs of every operand, or one element
-        // per access when A or x is not aligned to its elements
+        // grouped launch: 16-byte packs from any element; one element per
+        // access where rows are shorter than a pack or A or x is not aligned
+        // to its elements
         int v_item = p->vec;
         if (!p->persistent) {
-            if (q.n <= tile_stage_elems((int)es))
-                b.mode = kModeStaged, v_item = nv;
-            else if (q.m > 0 && q.n > 0 && fit_vec(nv, es, {q.A, q.x}) == nv)
-                b.mode = kModePacked, v_item = nv;
-            else
-                b.mode = kModeScalar, v_item = 1;
+            b.mode = q.n >= nv && fit_vec(nv, es, {q.A, q.x}) == nv ? kModePacked : kModeScalar;
+            v_item = b.mode == kModePacked ? nv : 1;
         } else {
             b.mode = p->vec == 1 ? kModeScalar : kModePacked;
         }
+        const bool tile = b.mode == kModePacked && !p->persistent;
         int64_t packs = std::max<int64_t>(1, ceil_div(q.n, v_item));
-        if (b.mode == kModeStaged && !p->persistent) // each lane owns up to packs_per_lane packs of its row
-            packs = ceil_div(packs, packs_per_lane);
-        int lanes = 1;
+        // each lane owns up to packs_per_lane packs of its row, 8 at most
+        // (513 bf16 with 16 packs 3.91 TB/s, with 8 4.48); rows of 4 KiB and more
+        // have all 64 lanes (2049 bf16 with 32 lanes 4.30, with 64 4.56)
+        if (tile && packs < 4 * 64)
+            packs = ceil_div(packs, std::min(packs_per_lane, 8));
+        int lanes = tile ? 8 : 1;
         while (lanes < 64 && lanes < packs)
             lanes <<= 1;
         b.lanes = lanes;
         if (q.m == 0)
             continue;
         int64_t rpi = std::max<int64_t>(1, std::min<int64_t>(q.m, kTileElems / std::max<int64_t>(1, q.n)));
-        if (b.mode == kModeStaged && !p->persistent) {
-            // whole row batches per tile: a staged work-group holds block / lanes
-            // rows at a time, so a tile of a multiple of that leaves no slot idle
-            const int64_t slots = std::max<int64_t>(1, p->block / lanes);
-            if (rpi > slots)
-                rpi = rpi / slots * slots;
-            p->stage_bytes = std::max(p->stage_bytes, tile_stage_bytes((int)es, q.n, lanes));
+        if (tile) {
+            // whole passes: a wave carries kTileRows * 64 / lanes rows at a time
+            const int64_t wave_rows = kTileRows * (64 / lanes), group_rows = wave_rows * (p->block / 64);
+            rpi = rpi >= group_rows ? rpi / group_rows * group_rows : std::max(wave_rows, rpi / wave_rows * wave_rows);
         }
         for (int64_t r0 = 0; r0 < q.m; r0 += rpi) {
             Work w{};
             w.it.kind = 0;
-            w.it.pad = b.mode == kModeStaged ? 0 : 1; // sort key: staged tiles first
+            w.it.pad = tile ? 0 : 1; // sort key: tiles read in packs first
             w.it.prob = i;
             w.it.begin = r0;
             w.it.end = std::min(q.m, r0 + rpi);
@@ -1768,7 +1764,7 @@ bwla_status bwla_batch_plan_create(bwla_dtype t, bwla_acc acc, bwla_dtype out_t,
         });
     for (const Work &w : work) {
         p->n_gemv_items += w.it.kind == 0;
-        p->n_staged_items += w.it.kind == 0 && w.it.pad == 0;
+        p->n_packed_items += w.it.kind == 0 && w.it.pad == 0;
     }
     for (Work &w : work)
         w.it.pad = 0;
@@ -1793,7 +1789,7 @@ bwla_status bwla_batch_plan_create(bwla_dtype t, bwla_acc acc, bwla_dtype out_t,
         p->grid = (int)std::max<int64_t>(1, p->n_items); // one work-group per item
     }
     // the shape logged: work items and the plan's algorithmic bytes; unroll
-    // is the packs per lane of the staged GEMV tiles
+    // is the packs per lane of the GEMV tiles
     log_call("batch plan", t, acc, p->n_items, (int64_t)total,
              Cfg{p->block, p->vec, packs_per_lane, p->grid, 0, 1, 1});
 

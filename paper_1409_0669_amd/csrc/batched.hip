@@ -128,27 +128,27 @@ __global__ __launch_bounds__(1024) void k_batched(BatchArgs a)
 // largest-first queue would -- without a software loop over items, without
 // atomics, and with barriers only in straight-line code.
 // ---------------------------------------------------------------------------
-// Rows of one GEMV tile, one G-lane group per row as in gemv_tile, but each
-// group carries kTileRowsInFlight rows at once and each lane kTilePacksInFlight
-// packs of each row, so that one trip issues all their loads (and the shared
-// packs of x) before any arithmetic.  Loop control is wave-uniform; rows past
-// the tile re-read its last row and are not stored.  No barriers.
+// Rows of one GEMV tile, one element per access (operands not aligned to their
+// elements, rows shorter than a pack): one G-lane group per row as in
+// gemv_tile, but each group carries kTileRowsInFlight rows at once and each
+// lane kTileElemsInFlight elements of each row.  Loop control is wave-uniform
+// up to the last trip; rows past the tile re-read its last row and are not stored.
 constexpr int kTileRowsInFlight = 4;
-constexpr int kTilePacksInFlight = 2;
+constexpr int kTileElemsInFlight = 2;
 
-template <typename T, int V, bool COMP>
-__device__ __forceinline__ void gemv_tile_block(const BatchGemv &g, int64_t rb, int64_t re, int out_f64)
+template <typename T, bool COMP>
+__device__ __forceinline__ void gemv_tile_scalar(const BatchGemv &g, int64_t rb, int64_t re, int out_f64)
 {
     using C = compute_t<T>;
     constexpr bool EXACT = std::is_same<T, bf16_t>::value;
-    constexpr int RB = kTileRowsInFlight, U = kTilePacksInFlight;
+    constexpr int RB = kTileRowsInFlight, U = kTileElemsInFlight;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
     const int G = g.lanes;
     const int rpw = 64 / G;
     const int sub = lane / G, gl = lane - sub * G;
     const T *A = (const T *)g.A;
     const T *x = (const T *)g.x;
-    const int64_t K = g.n, kpack = K / V;
+    const int64_t K = g.n;
     const int64_t slots = (int64_t)nw * rpw; // rows the work-group holds per row batch
     for (int64_t base = rb + (int64_t)wave * rpw; base < re; base += RB * slots) {
         const T *row[RB];
@@ -158,38 +158,24 @@ __device__ __forceinline__ void gemv_tile_block(const BatchGemv &g, int64_t rb, 
             row[j] = A + (r < re ? r : re - 1) * g.lda;
         }
         acc_t<T, COMP> acc[RB];
-        int64_t p = gl;
-        for (; p + (int64_t)(U - 1) * G < kpack; p += (int64_t)U * G) {
-            Pack<T, V> xv[U], av[RB][U];
+        int64_t k = gl;
+        for (; k + (int64_t)(U - 1) * G < K; k += (int64_t)U * G) {
+            T xv[U], av[RB][U];
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                xv[u] = load_pack<T, V>(x + (p + (int64_t)u * G) * V);
+                xv[u] = x[k + (int64_t)u * G];
 #pragma unroll
             for (int j = 0; j < RB; ++j)
 #pragma unroll
                 for (int u = 0; u < U; ++u)
-                    av[j][u] = load_pack_nt<T, V>(row[j] + (p + (int64_t)u * G) * V);
+                    av[j][u] = row[j][k + (int64_t)u * G];
 #pragma unroll
             for (int j = 0; j < RB; ++j)
 #pragma unroll
                 for (int u = 0; u < U; ++u)
-#pragma unroll
-                    for (int e = 0; e < V; ++e)
-                        acc[j].template add_prod<EXACT>(widen(av[j][u].v[e]), widen(xv[u].v[e]));
+                    acc[j].template add_prod<EXACT>(widen(av[j][u]), widen(xv[u]));
         }
-        for (; p < kpack; p += G) {
-            const Pack<T, V> xv = load_pack<T, V>(x + p * V);
-            Pack<T, V> av[RB];
-#pragma unroll
-            for (int j = 0; j < RB; ++j)
-                av[j] = load_pack_nt<T, V>(row[j] + p * V);
-#pragma unroll
-            for (int j = 0; j < RB; ++j)
-#pragma unroll
-                for (int e = 0; e < V; ++e)
-                    acc[j].template add_prod<EXACT>(widen(av[j].v[e]), widen(xv.v[e]));
-        }
-        for (int64_t k = kpack * V + gl; k < K; k += G) {
+        for (; k < K; k += G) {
             const C xk = widen(x[k]);
 #pragma unroll
             for (int j = 0; j < RB; ++j)
@@ -207,160 +193,101 @@ __device__ __forceinline__ void gemv_tile_block(const BatchGemv &g, int64_t rb, 
     }
 }
 
-// GEMV tile with x staged in LDS, for rows of at most tile_stage_elems()
-// entries.  Rows may start anywhere (lda need not keep them 16-byte
-// aligned): each row is read as a head of h < V elements up to its first
-// 16-byte boundary, then whole 16-byte packs, then a tail of fewer than V
-// elements, and the x entry of every A entry comes from LDS.  x is held
-// interleaved by column residue, xs[(c % V) * P + c / V], so the lanes of a
-// group -- which take consecutive packs -- read consecutive LDS words for each
-// element position of a pack, whatever the row's head.  The residue stride P
-// is congruent to G modulo 64, so groups of one wave whose rows start at
-// different residues read disjoint banks.
+// Rows of one GEMV tile in 16-byte packs from any element: a row belongs to a
+// group of G lanes (a compile-time constant), and a wave carries R = 8 rows
+// per group, 512 / G rows, with one pack of each in flight per trip, so that a
+// pack of x (from the caches) is read and widened once for 8 rows.  The last
+// trip is masked: its packs end with the row, and entries that an earlier pack
+// covered, or past the end, count as 0 on both sides.  No LDS and no
+// barrier; loop control is wave-uniform; rows past the tile re-read its last
+// row and are not stored.
 //
-// A row belongs to a group of G lanes (a compile-time constant here, so every
-// LDS and global offset within a trip is an immediate), G sized on the host
-// so that each lane owns about the plan's packs per lane (the batch table
-// entry's unroll, kStagedPacks by default) of it.  One trip issues the
-// U packs of A and their U*V x entries before any arithmetic; two
-// accumulators per lane split the dependency chain.  Loop control is
-// wave-uniform; rows past the tile re-read its last row and are not stored.
-template <typename T, int V, bool COMP, int G>
-__device__ __forceinline__ void staged_rows(const BatchGemv &g, int64_t rb, int64_t re, int out_f64,
-                                            const compute_t<T> *xs, int P)
+// Bound by HBM once a row is some KiB long, below that by the work per row
+// beside its packs.  The 8 sums of a group are reduced together, each of the
+// first three exchanges leaving a lane with half of them: 4 + 2 + 1 sums and
+// one per further lane bit, 10 for 8 rows of 64 lanes where a butterfly of
+// each takes 48.  With fewer than 64 lanes a trip covers 128 to 512 bytes of a
+// row, whose lines the next trip reads on where rows start anywhere: those
+// loads are not marked as streaming, so that the line is still there (rows of
+// 257 bf16 2.9 -> 3.8 TB/s, of 513 f32 4.65 -> 4.84; with 64 lanes streaming
+// loads are the faster, 513 f64 5.36 -> 5.57).
+//
+// The form this replaced staged x in LDS and read a row as head, aligned packs
+// and tail.  GEMV kernels of uneven batches (rows and columns 32 to 4096),
+// before -> after: 512 compensated bf16, 765 MB, 212 -> 142 us (5.4 TB/s); 256 f32,
+// 699 MB, 146 -> 122; 128 f64, 912 MB, 185 -> 153; 20 f64, 120 MB, 74 -> 33; 40
+// compensated bf16, 75 MB, 35 -> 21.
+template <typename T, bool COMP, int G>
+__device__ __forceinline__ void gemv_tile_rows(const BatchGemv &g, int64_t rb, int64_t re, int out_f64)
 {
-    using C = compute_t<T>;
     constexpr bool EXACT = std::is_same<T, bf16_t>::value;
-    // packs in flight per trip: 8 for 2-element packs, 4 for 4- and
-    // 8-element packs (whose x values per trip would not fit the registers)
-    constexpr int U = V >= 4 ? 4 : 8;
-    constexpr int RPW = 64 / G;
-    const int n = (int)g.n;
+    constexpr int V = 16 / (int)sizeof(T), R = kTileRows, RPW = 64 / G;
+    constexpr bool NT = G == 64;
+    const int64_t n = g.n;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
     const int sub = lane / G, gl = lane % G;
     const T *A = (const T *)g.A;
-    const int64_t slots = (int64_t)nw * RPW;
-    for (int64_t base = rb + (int64_t)wave * RPW; base < re; base += slots) {
-        const int64_t r = base + sub;
-        const T *row = A + (r < re ? r : re - 1) * g.lda;
-        const int mis = (int)(((uintptr_t)row & 15) / sizeof(T)); // elements past a 16-byte boundary
-        const int h = mis ? (V - mis < n ? V - mis : n) : 0;
-        const int np = (n - h) / V;
-        const int t0 = h + np * V;
-        // head (h < V elements before the first 16-byte boundary) and tail
-        // (< V elements after the last whole pack): lane gl takes element gl
-        // of each; rows with G < V lanes finish them after the packs
-        const T hv = gl < h ? row[gl] : T(0);
-        const T tv = t0 + gl < n ? row[t0 + gl] : T(0);
-        // x entry of element e of this lane's k-th pack (column
-        // h + (gl + k G) V + e): xs[xo[e] + k G].  Word offsets from the LDS
-        // array itself (not pointers advanced in the loop), so that the
-        // reads stay LDS reads with immediate offsets.
-        int xo[V];
+    const T *x = (const T *)g.x;
+    const int64_t whole = n / (G * V) * (G * V); // entries of the unmasked trips
+    // the masked trip: this lane's pack starts at `last`, its first `skip`
+    // entries (all of them past the end) are another pack's
+    const int64_t want = whole + gl * V;
+    const int64_t last = want + V <= n ? want : n - V;
+    const int skip = want - last < V ? (int)(want - last) : V;
+    for (int64_t base = rb + (int64_t)wave * (R * RPW); base < re; base += (int64_t)nw * (R * RPW)) {
+        const T *row[R];
 #pragma unroll
-        for (int e = 0; e < V; ++e)
-            xo[e] = ((h + e) % V) * P + (h + e) / V + gl;
-        const T *ap = row + h + (int64_t)gl * V;
-        acc_t<T, COMP> acc[2];
-        int p = gl;
-        for (; p + (U - 1) * G < np; p += U * G) {
-            Pack<T, V> av[U];
-            C xv[U][V];
+        for (int j = 0; j < R; ++j) {
+            const int64_t r = base + j * RPW + sub;
+            row[j] = A + (r < re ? r : re - 1) * g.lda;
+        }
+        acc_t<T, COMP> acc[R];
+        for (int64_t k = gl * V; k < whole; k += G * V) {
+            Pack<T, V> a[R];
+            const Pack<T, V> xv = load_pack<T, V>(x + k);
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-                av[u] = load_pack_nt<T, V>(ap + u * G * V);
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-#pragma unroll
-                for (int e = 0; e < V; ++e)
-                    xv[u][e] = xs[xo[e] + u * G];
+            for (int j = 0; j < R; ++j)
+                a[j] = load_pack<T, V, NT>(row[j] + k);
             end_of_loads();
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-#pragma unroll
-                for (int e = 0; e < V; ++e)
-                    acc[u & 1].template add_prod<EXACT>(widen(av[u].v[e]), xv[u][e]);
-            ap += U * G * V;
-#pragma unroll
             for (int e = 0; e < V; ++e)
-                xo[e] += U * G;
+#pragma unroll
+                for (int j = 0; j < R; ++j)
+                    acc[j].template add_prod<EXACT>(widen(a[j].v[e]), widen(xv.v[e]));
         }
-        for (; p < np; p += G) {
-            const Pack<T, V> a = load_pack_nt<T, V>(ap);
-            C xv[V];
+        if (whole < n) {
+            Pack<T, V> a[R];
+            const Pack<T, V> xv = load_pack<T, V>(x + last);
 #pragma unroll
-            for (int e = 0; e < V; ++e)
-                xv[e] = xs[xo[e]];
-#pragma unroll
-            for (int e = 0; e < V; ++e)
-                acc[0].template add_prod<EXACT>(widen(a.v[e]), xv[e]);
-            ap += G * V;
-#pragma unroll
-            for (int e = 0; e < V; ++e)
-                xo[e] += G;
-        }
-        if (gl < h)
-            acc[1].template add_prod<EXACT>(widen(hv), xs[(gl % V) * P + gl / V]);
-        if (t0 + gl < n)
-            acc[1].template add_prod<EXACT>(widen(tv), xs[((t0 + gl) % V) * P + (t0 + gl) / V]);
-        for (int k = gl + G; k < h; k += G) // only when G < V
-            acc[1].template add_prod<EXACT>(widen(row[k]), xs[(k % V) * P + k / V]);
-        for (int k = t0 + gl + G; k < n; k += G)
-            acc[1].template add_prod<EXACT>(widen(row[k]), xs[(k % V) * P + k / V]);
-        DD d = combine<COMP>(acc[0].to_dd(), acc[1].to_dd());
-#pragma unroll
-        for (int m = G >> 1; m >= 1; m >>= 1)
-            d = combine<COMP>(d, shfl_xor_dd(d, m));
-        if (gl == 0 && r < re)
-            store_out(g.y, r, out_f64, d.hi + d.lo);
-    }
-}
-
-// Stages x (widened to the compute type) in LDS, then runs the rows of the
-// tile with the row-group size the host chose.  Contains a barrier: every
-// thread of the work-group calls it.
-template <typename T, int V, bool COMP>
-__device__ __forceinline__ void gemv_tile_staged(const BatchGemv &g, int64_t rb, int64_t re, int out_f64,
-                                                 compute_t<T> *xs)
-{
-    using C = compute_t<T>;
-    // Each thread stages whole pack columns q (x entries qV .. qV + V - 1 to
-    // words e * P + q), SQ columns per round so that 8 entries are in flight:
-    // consecutive threads then write consecutive words of each residue row,
-    // free of bank conflicts whatever P is.
-    constexpr int SQ = V >= 8 ? 1 : 8 / V;
-    const int n = (int)g.n;
-    const int G = __builtin_amdgcn_readfirstlane(g.lanes);
-    const int P = staged_stride(n, V, G);
-    const int nq = (n + V - 1) / V;
-    const T *x = (const T *)g.x;
-    for (int q0 = threadIdx.x; q0 < nq; q0 += SQ * blockDim.x) {
-        C v[SQ][V];
-#pragma unroll
-        for (int k = 0; k < SQ; ++k)
+            for (int j = 0; j < R; ++j)
+                a[j] = load_pack<T, V, NT>(row[j] + last);
+            end_of_loads();
 #pragma unroll
             for (int e = 0; e < V; ++e) {
-                const int c = (q0 + k * (int)blockDim.x) * V + e;
-                v[k][e] = c < n ? widen(x[c]) : C(0);
+                const T xe = e >= skip ? xv.v[e] : T(0);
+#pragma unroll
+                for (int j = 0; j < R; ++j)
+                    acc[j].template add_prod<EXACT>(widen(e >= skip ? a[j].v[e] : T(0)), widen(xe));
             }
-#pragma unroll
-        for (int k = 0; k < SQ; ++k) {
-            const int q = q0 + k * (int)blockDim.x;
-            if (q < nq)
-#pragma unroll
-                for (int e = 0; e < V; ++e)
-                    xs[e * P + q] = v[k][e];
         }
-    }
-    __syncthreads();
-    switch (G) {
-    case 1: staged_rows<T, V, COMP, 1>(g, rb, re, out_f64, xs, P); break;
-    case 2: staged_rows<T, V, COMP, 2>(g, rb, re, out_f64, xs, P); break;
-    case 4: staged_rows<T, V, COMP, 4>(g, rb, re, out_f64, xs, P); break;
-    case 8: staged_rows<T, V, COMP, 8>(g, rb, re, out_f64, xs, P); break;
-    case 16: staged_rows<T, V, COMP, 16>(g, rb, re, out_f64, xs, P); break;
-    case 32: staged_rows<T, V, COMP, 32>(g, rb, re, out_f64, xs, P); break;
-    default: staged_rows<T, V, COMP, 64>(g, rb, re, out_f64, xs, P); break;
+        DD d[R];
+#pragma unroll
+        for (int j = 0; j < R; ++j)
+            d[j] = acc[j].to_dd();
+        constexpr int B = G == 64 ? 5 : G == 32 ? 4 : G == 16 ? 3 : 2; // highest lane bit of a group
+        halve<COMP, B, 4>(d, lane);
+        halve<COMP, B - 1, 2>(d, lane);
+        halve<COMP, B - 2, 1>(d, lane);
+        if constexpr (B > 4)
+            d[0] = combine<COMP>(d[0], dpp_dd<kDppHalfMirror>(d[0]));
+        if constexpr (B > 3)
+            d[0] = combine<COMP>(d[0], dpp_dd<kDppXor2>(d[0]));
+        if constexpr (B > 2)
+            d[0] = combine<COMP>(d[0], dpp_dd<kDppXor1>(d[0]));
+        const int j = gl / (G / 8); // the row this lane's sum belongs to
+        const int64_t r = base + j * RPW + sub;
+        if (gl % (G / 8) == 0 && r < re)
+            store_out(g.y, r, out_f64, d[0].hi + d[0].lo);
     }
 }
 
@@ -413,37 +340,28 @@ __device__ __forceinline__ void dot_chunk_block(const BatchArgs &a, const BatchI
     }
 }
 
-// Three kernels: staged GEMV items (a.items[0, a.n_staged_items)), the
-// other GEMV items (up to a.n_gemv_items) and dot items (the rest), so that
-// each gets the registers (and the staged tiles the LDS) of its own code
-// paths.  The staged kernel's x stage is dynamic LDS, sized by the plan for
-// its longest staged x.  Its waits on memory and LDS are hidden by other
-// waves, so it asks for 6 waves per SIMD where that costs no spills (f32:
-// 79 VGPRs); the bf16 and f64 forms are left to the compiler (98-130
-// VGPRs; asked for more waves, they spill).
-template <typename T, bool COMP>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(std::is_same<T, float>::value ? 6 : 1, 8)))
-void k_grouped_gemv_staged(BatchArgs a)
-{
-    using C = compute_t<T>;
-    constexpr int NATIVE = 16 / (int)sizeof(T);
-    extern __shared__ __attribute__((aligned(16))) char stage[];
-    const BatchItem w = a.items[blockIdx.x];
-    gemv_tile_staged<T, NATIVE, COMP>(a.gemv[w.prob], w.begin, w.end, a.out_f64, reinterpret_cast<C *>(stage));
-}
-
+// Three kernels: GEMV items in packs (a.items[0, a.n_packed_items)), the other
+// GEMV items (up to a.n_gemv_items) and dot items (the rest), so that each
+// gets the registers of its own code paths.
 template <typename T, bool COMP>
 __global__ __launch_bounds__(512) void k_grouped_gemv(BatchArgs a)
 {
-    constexpr int NATIVE = 16 / (int)sizeof(T);
-    const BatchItem w = a.items[a.n_staged_items + blockIdx.x];
+    const BatchItem w = a.items[blockIdx.x];
     const BatchGemv &g = a.gemv[w.prob];
     // the item is the same for every thread of the work-group
-    const int mode = __builtin_amdgcn_readfirstlane(g.mode);
-    if (mode == kModePacked)
-        gemv_tile_block<T, NATIVE, COMP>(g, w.begin, w.end, a.out_f64);
-    else
-        gemv_tile_block<T, 1, COMP>(g, w.begin, w.end, a.out_f64);
+    switch (__builtin_amdgcn_readfirstlane(g.lanes)) {
+    case 8: gemv_tile_rows<T, COMP, 8>(g, w.begin, w.end, a.out_f64); break;
+    case 16: gemv_tile_rows<T, COMP, 16>(g, w.begin, w.end, a.out_f64); break;
+    case 32: gemv_tile_rows<T, COMP, 32>(g, w.begin, w.end, a.out_f64); break;
+    default: gemv_tile_rows<T, COMP, 64>(g, w.begin, w.end, a.out_f64); break;
+    }
+}
+
+template <typename T, bool COMP>
+__global__ __launch_bounds__(512) void k_grouped_gemv_scalar(BatchArgs a)
+{
+    const BatchItem w = a.items[a.n_packed_items + blockIdx.x];
+    gemv_tile_scalar<T, COMP>(a.gemv[w.prob], w.begin, w.end, a.out_f64);
 }
 
 template <typename T, bool COMP>
@@ -505,18 +423,17 @@ hipError_t launch_batched(const BatchArgs &a, bool comp, int grid, int block, hi
 template hipError_t launch_batched<BWLA_T>(const BatchArgs &, bool, int, int, hipStream_t);
 
 template <typename T>
-hipError_t launch_grouped(const BatchArgs &a, bool comp, int block, size_t stage_bytes, hipStream_t s)
+hipError_t launch_grouped(const BatchArgs &a, bool comp, int block, hipStream_t s)
 {
     return with_bool(comp, [&](auto CP) {
-        const int64_t ng = a.n_gemv_items - a.n_staged_items, nd = a.n_items - a.n_gemv_items;
-        if (a.n_staged_items > 0)
-            hipLaunchKernelGGL((k_grouped_gemv_staged<T, CP.value>), dim3((unsigned)a.n_staged_items), dim3(block),
-                               (unsigned)stage_bytes, s, a);
+        const int64_t np = a.n_packed_items, ng = a.n_gemv_items - np, nd = a.n_items - a.n_gemv_items;
+        if (np > 0)
+            hipLaunchKernelGGL((k_grouped_gemv<T, CP.value>), dim3((unsigned)np), dim3(block), 0, s, a);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess)
             return e;
         if (ng > 0)
-            hipLaunchKernelGGL((k_grouped_gemv<T, CP.value>), dim3((unsigned)ng), dim3(block), 0, s, a);
+            hipLaunchKernelGGL((k_grouped_gemv_scalar<T, CP.value>), dim3((unsigned)ng), dim3(block), 0, s, a);
         e = hipGetLastError();
         if (e != hipSuccess || nd <= 0)
             return e;
@@ -525,7 +442,7 @@ hipError_t launch_grouped(const BatchArgs &a, bool comp, int block, size_t stage
     });
 }
 
-template hipError_t launch_grouped<BWLA_T>(const BatchArgs &, bool, int, size_t, hipStream_t);
+template hipError_t launch_grouped<BWLA_T>(const BatchArgs &, bool, int, hipStream_t);
 
 #if BWLA_T_IS_F64
 hipError_t launch_batch_reset(unsigned *counters, int64_t count, hipStream_t s)

@@ -369,6 +369,25 @@ template <bool COMP, int M> __device__ __forceinline__ DD pair_sum(DD a, DD b)
     return combine<COMP>(a, b);
 }
 
+// Sums of 2 N values over the lane pairs that differ in bit BIT: each lane is
+// left with N of them in d[0 .. N - 1], the upper half where its bit is set.  (Below
+// bit 4 the pair is exchanged by selects and one DPP move; the half mirror
+// pairs lanes 7 apart from the other end, which a sum over all 8 may use.)
+template <bool COMP, int BIT, int N> __device__ __forceinline__ void halve(DD *d, int lane)
+{
+#pragma unroll
+    for (int e = 0; e < N; ++e) {
+        if constexpr (BIT >= 4) {
+            d[e] = pair_sum<COMP, 1 << BIT>(d[e], d[e + N]);
+        } else {
+            constexpr int CTRL = BIT == 3 ? kDppXor8 : BIT == 2 ? kDppHalfMirror : BIT == 1 ? kDppXor2 : kDppXor1;
+            const bool up = lane & (1 << BIT);
+            const DD keep = up ? d[e + N] : d[e], give = up ? d[e] : d[e + N];
+            d[e] = combine<COMP>(keep, dpp_dd<CTRL>(give));
+        }
+    }
+}
+
 // Sum over one work-group (blockDim.x a multiple of 64, at most 1024).  `lds`
 // holds at least 16 DD.  The result is valid in every thread.  Contains
 // barriers: every thread of the block must call it.

@@ -442,7 +442,7 @@ def _ger_candidates(dtype, quick):
 
 
 def _batch_candidates(quick):
-    # the work-group size and the packs of a GEMV row each lane of a staged
+    # the work-group size and the packs of a GEMV row each lane of a
     # tile owns (fewer packs: more lanes share a row)
     return [dict(block=b, unroll=u) for b in ((256, 512) if quick else (128, 256, 512))
             for u in ((8, 16) if quick else (4, 8, 16, 32))]
