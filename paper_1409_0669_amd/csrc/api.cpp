@@ -267,10 +267,11 @@ Cfg resolve_vector(int op, int t, int acc, int64_t n, std::initializer_list<cons
 // work-groups are otherwise too many to dispatch (16000 x 100 f64 4.9 against 7.8).
 //
 // From 256 MiB on: 1024 threads with one pack of each of two lines where long
-// lines fill them evenly (8192 x 8192 f64 76.9 us against 78.5 at 512), else 512
-// threads; the compensated forms as few threads as take 8 packs each (16384 x 16384
-// bf16 83.8 us at 256 threads, 116 at 512; 20001 x 5000 f32 64.9 at 256, 86.8 at 512),
-// and four long f64 or bf16 lines (f64 300 us at 16384 x 16384, 303 with two; bf16 90, 97).
+// lines fill them evenly, f64 from 1 GiB (at 8192 x 8192 79.4 us, and 79.5 for 512
+// threads with four lines, whose form with the dot is the faster: a solver's
+// iteration 87.7 us against 88.0), else 512 threads; the compensated forms as
+// few threads as take 8 packs each (16384 x 16384 bf16 83.8 us at 256 threads, 116
+// at 512; 20001 x 5000 f32 64.9 at 256, 86.8 at 512), and four long f64 or bf16 lines (f64 300 us at 16384 x 16384, 303 with two; bf16 90, 97).
 // With the dot epilogue four lines always: fewer work-groups have its tail
 // (8192 x 8192 f64 80.5 us, 81.8 with two).  A line's sum does not depend on it.
 Cfg rows_rule(int t, int acc, int64_t L, int64_t K, bool with_dot)
@@ -292,6 +293,8 @@ Cfg rows_rule(int t, int acc, int64_t L, int64_t K, bool with_dot)
                 c.block /= 2;
             if (t != BWLA_F32 && packs >= 2048)
                 c.rows = 4;
+        } else if (packs >= 3584 && even && t == BWLA_F64 && bytes < 1024 * mib) {
+            c.rows = 4;
         } else if (packs >= 3584 && even) {
             c.block = 1024;
             c.unroll = 1;
