@@ -320,12 +320,11 @@ bwla_status bwla_workspace_size(bwla_op op, bwla_dtype t, bwla_acc acc, bwla_lay
 /* ---- batched uneven problems ---------------------------------------------
  * A plan holds many row-major GEMVs (y = A x, out_t output) and many dots
  * (out = <x, y>, out_t output) of one storage type.  Work is flattened into
- * items (row tiles of a GEMV, chunks of a dot) ordered largest first and run
- * with one work-group per item, one launch per kind of item (GEMV tiles read
- * in 16-byte packs, the other GEMV tiles, dot chunks; the hardware dispatcher
- * hands out each launch's items in order).  Each dot's chunk partials are
- * combined in chunk order by a finalize kernel, so results do not depend on
- * the batch order or on scheduling.
+ * items (row tiles of a GEMV, then chunks of a dot, each largest first) and
+ * run in one launch with one work-group per item (the hardware dispatcher
+ * hands them out in order).  Each dot's chunk partials are combined in a fixed
+ * order by a finalize kernel, where a dot has more than one, so results do
+ * not depend on the batch order or on scheduling.
  * create: copies the descriptors to the device and allocates the plan's own
  *         counters and partial slots (the only allocating call; not allowed
  *         while `stream` capture is active).

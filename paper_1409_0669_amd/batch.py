@@ -1,8 +1,7 @@
 """``BatchPlan``: many uneven row-major GEMVs and dots in one batched launch --
-one work-group per work item (row tiles of the GEMVs, chunks of the dots,
-largest first), one kernel per kind of item (GEMV tiles read in
-16-byte packs, the other GEMV tiles, dot chunks), then a finalize kernel that combines each
-dot's chunk partials in chunk order -- optionally captured in a HIP graph and
+one work-group per work item (row tiles of the GEMVs, then chunks of the dots,
+each largest first), then a finalize kernel that combines the chunk partials
+of longer dots in a fixed order -- optionally captured in a HIP graph and
 replayed.  The work-group size and the packs of a GEMV row each lane owns come
 from the tuning table's batch entry unless given."""
 from __future__ import annotations

@@ -1514,8 +1514,7 @@ struct bwla_batch_plan {
     int device = 0;
     int grid = 0, block = 256, vec = 1;
     int64_t n_items = 0, n_dots = 0;
-    int64_t n_gemv_items = 0; // grouped launch: GEMV items come first
-    int64_t n_packed_items = 0; // of those, the tiles read in packs come first
+    bool finalize = false; // a dot has more than one chunk
     double bytes = 0;
     BatchItem *d_items = nullptr;
     BatchGemv *d_gemv = nullptr;
@@ -1567,8 +1566,6 @@ hipError_t enqueue_batch(bwla_batch_plan *p, hipStream_t s)
     BatchArgs a;
     a.items = p->d_items;
     a.n_items = p->n_items;
-    a.n_gemv_items = p->n_gemv_items;
-    a.n_packed_items = p->n_packed_items;
     a.gemv = p->d_gemv;
     a.dots = p->d_dots;
     a.partials = p->d_partials;
@@ -1581,7 +1578,7 @@ hipError_t enqueue_batch(bwla_batch_plan *p, hipStream_t s)
             return launch_batched<T>(a, p->acc == BWLA_ACC_COMPENSATED, p->grid, p->block, s);
         return launch_grouped<T>(a, p->acc == BWLA_ACC_COMPENSATED, p->block, s);
     });
-    if (e != hipSuccess)
+    if (e != hipSuccess || !p->finalize)
         return e;
     return launch_batch_finalize(p->d_dots, p->n_dots, p->d_partials, p->acc == BWLA_ACC_COMPENSATED,
                                  p->out_t == BWLA_F64, s);
@@ -1674,7 +1671,9 @@ bwla_status bwla_batch_plan_create(bwla_dtype t, bwla_acc acc, bwla_dtype out_t,
     // work-group each in the grouped launch.  Chunk starts stay multiples of
     // 64 * 16 elements, so every chunk begins on a pack boundary.
     const int64_t kTileElems = p->persistent ? (1 << 15) : (1 << 16); // elements of A per GEMV row tile
-    const int64_t kChunk = p->persistent ? (1 << 14) : (1 << 16);     // elements per dot chunk
+    // elements per dot chunk: 64 KiB of each operand (20 f32 dots 15.0 us with
+    // 256 KiB, 8.0 with 64; large batches the same: 4096 bf16 dots 339 and 342)
+    const int64_t kChunk = p->persistent ? (1 << 14) : (1 << 16) / (int64_t)es;
 
     for (int i = 0; i < ng; ++i) {
         const bwla_gemv_desc &q = g[i];
@@ -1717,7 +1716,6 @@ bwla_status bwla_batch_plan_create(bwla_dtype t, bwla_acc acc, bwla_dtype out_t,
         for (int64_t r0 = 0; r0 < q.m; r0 += rpi) {
             Work w{};
             w.it.kind = 0;
-            w.it.pad = tile ? 0 : 1; // sort key: tiles read in packs first
             w.it.prob = i;
             w.it.begin = r0;
             w.it.end = std::min(q.m, r0 + rpi);
@@ -1751,26 +1749,18 @@ bwla_status bwla_batch_plan_create(bwla_dtype t, bwla_acc acc, bwla_dtype out_t,
             work.push_back(w);
         }
         slots += b.chunks;
+        p->finalize = p->finalize || b.chunks > 1;
         p->bytes += 2.0 * q.n * es + os;
     }
-    // Largest first.  The grouped launch runs GEMV tiles and dot chunks as two
-    // kernels, so it orders by kind first.
+    // Largest first; in the grouped launch GEMV tiles, then dot chunks.
     if (p->persistent)
         std::stable_sort(work.begin(), work.end(), [](const Work &a, const Work &b) { return a.cost > b.cost; });
     else
         std::stable_sort(work.begin(), work.end(), [](const Work &a, const Work &b) {
             if (a.it.kind != b.it.kind)
                 return a.it.kind < b.it.kind;
-            if (a.it.pad != b.it.pad)
-                return a.it.pad < b.it.pad;
             return a.cost > b.cost;
         });
-    for (const Work &w : work) {
-        p->n_gemv_items += w.it.kind == 0;
-        p->n_packed_items += w.it.kind == 0 && w.it.pad == 0;
-    }
-    for (Work &w : work)
-        w.it.pad = 0;
     std::vector<BatchItem> items(work.size());
     for (size_t i = 0; i < work.size(); ++i)
         items[i] = work[i].it;

@@ -291,18 +291,18 @@ __device__ __forceinline__ void gemv_tile_rows(const BatchGemv &g, int64_t rb, i
     }
 }
 
-// One dot chunk reduced by a whole work-group: each thread keeps
-// kChunkPacksInFlight packs of both operands in flight per trip, two
-// accumulators, then the work-group tree (block_sum, barriers in
-// straight-line code).
-constexpr int kChunkPacksInFlight = 8;
+// One dot chunk reduced by a whole work-group: each thread keeps U packs of
+// both operands in flight per trip, two accumulators, then the work-group
+// tree (block_sum, barriers in straight-line code).  U is 8, and 4 in the
+// compensated bf16 form, which then fits 4 waves per SIMD (512 GEMVs and 4096 dots
+// 485 us with 8, 473 with 4; the f32 form loses, 471 and 476).
 
 template <typename T, int V, bool COMP>
 __device__ __forceinline__ void dot_chunk_block(const BatchArgs &a, const BatchItem &w, DD *lds)
 {
     using C = compute_t<T>;
     constexpr bool EXACT = std::is_same<T, bf16_t>::value;
-    constexpr int U = kChunkPacksInFlight;
+    constexpr int U = EXACT && COMP ? 4 : 8;
     const BatchDot &d = a.dots[w.prob];
     const T *x = (const T *)d.x, *y = (const T *)d.y;
     acc_t<T, COMP> acc[2];
@@ -340,41 +340,37 @@ __device__ __forceinline__ void dot_chunk_block(const BatchArgs &a, const BatchI
     }
 }
 
-// Three kernels: GEMV items in packs (a.items[0, a.n_packed_items)), the other
-// GEMV items (up to a.n_gemv_items) and dot items (the rest), so that each
-// gets the registers of its own code paths.
+// Every item of a plan in one launch: GEMV tiles first, whose rows are the
+// longer serial chains, then dot chunks, which fill the CUs the tiles leave.
+// With a launch per kind each kind's last work-groups ran alone.  GEMV and dot
+// kernels -> this one, with dot chunks of 64 KiB for 128 and more: 20 GEMVs and 20 dots f32
+// 18.2 + 15.0 -> 18.7 us, 20 and 80 f64 32.7 + 33.1 -> 51.8, 8 and 32 bf16 9.2 + 12.4 -> 9.6,
+// 512 and 4096 compensated bf16 144 + 339 -> 473 (3.07 GB, 6.5 TB/s).
 template <typename T, bool COMP>
-__global__ __launch_bounds__(512) void k_grouped_gemv(BatchArgs a)
+__global__ __launch_bounds__(512) void k_grouped(BatchArgs a)
 {
-    const BatchItem w = a.items[blockIdx.x];
-    const BatchGemv &g = a.gemv[w.prob];
+    constexpr int NATIVE = 16 / (int)sizeof(T);
+    __shared__ DD lds[16];
     // the item is the same for every thread of the work-group
+    const BatchItem w = a.items[blockIdx.x];
+    if (__builtin_amdgcn_readfirstlane(w.kind) == 1) { // block_sum holds barriers
+        if (__builtin_amdgcn_readfirstlane(a.dots[w.prob].mode) == kModePacked)
+            dot_chunk_block<T, NATIVE, COMP>(a, w, lds);
+        else
+            dot_chunk_block<T, 1, COMP>(a, w, lds);
+        return;
+    }
+    const BatchGemv &g = a.gemv[w.prob];
+    if (__builtin_amdgcn_readfirstlane(g.mode) == kModeScalar) {
+        gemv_tile_scalar<T, COMP>(g, w.begin, w.end, a.out_f64);
+        return;
+    }
     switch (__builtin_amdgcn_readfirstlane(g.lanes)) {
     case 8: gemv_tile_rows<T, COMP, 8>(g, w.begin, w.end, a.out_f64); break;
     case 16: gemv_tile_rows<T, COMP, 16>(g, w.begin, w.end, a.out_f64); break;
     case 32: gemv_tile_rows<T, COMP, 32>(g, w.begin, w.end, a.out_f64); break;
     default: gemv_tile_rows<T, COMP, 64>(g, w.begin, w.end, a.out_f64); break;
     }
-}
-
-template <typename T, bool COMP>
-__global__ __launch_bounds__(512) void k_grouped_gemv_scalar(BatchArgs a)
-{
-    const BatchItem w = a.items[a.n_packed_items + blockIdx.x];
-    gemv_tile_scalar<T, COMP>(a.gemv[w.prob], w.begin, w.end, a.out_f64);
-}
-
-template <typename T, bool COMP>
-__global__ __launch_bounds__(512) void k_grouped_dot(BatchArgs a)
-{
-    constexpr int NATIVE = 16 / (int)sizeof(T);
-    __shared__ DD lds[16];
-    const BatchItem w = a.items[a.n_gemv_items + blockIdx.x];
-    const int mode = __builtin_amdgcn_readfirstlane(a.dots[w.prob].mode); // block_sum holds barriers
-    if (mode == kModePacked)
-        dot_chunk_block<T, NATIVE, COMP>(a, w, lds);
-    else
-        dot_chunk_block<T, 1, COMP>(a, w, lds);
 }
 
 #if BWLA_T_IS_F64 // type-independent kernels live in the f64 object only
@@ -385,23 +381,30 @@ __global__ void k_zero_counters(unsigned *c, int64_t count)
         c[i] = 0u;
 }
 
-// One thread per dot: combine the chunk partials of multi-chunk dots in
-// chunk order (single-chunk dots were written by the batched kernel).
+// One wave per dot: combine the chunk partials of multi-chunk dots, each
+// lane's in chunk order and then the lanes (single-chunk dots were written by
+// the chunk's work-group).  Bound by the chain of loads and sums: one thread
+// per dot took 0.5 us per chunk beyond 8.
 template <bool COMP>
 __global__ __launch_bounds__(256) void k_batch_finalize(const BatchDot *dots, int64_t nd, const DD *partials,
                                                         int out_f64)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int lane = threadIdx.x & 63;
+    const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     if (i >= nd)
         return;
     const BatchDot d = dots[i];
     if (d.chunks <= 1)
         return;
     const DD *p = partials + d.slot0;
-    DD t = p[0];
-    for (int c = 1; c < d.chunks; ++c)
+    DD t = {0.0, 0.0};
+    if (lane < d.chunks)
+        t = p[lane];
+    for (int c = lane + 64; c < d.chunks; c += 64)
         t = combine<COMP>(t, p[c]);
-    store_out(d.out, 0, out_f64, t.hi + t.lo);
+    t = wave_sum<COMP>(t);
+    if (lane == 0)
+        store_out(d.out, 0, out_f64, t.hi + t.lo);
 }
 #endif
 
@@ -426,18 +429,7 @@ template <typename T>
 hipError_t launch_grouped(const BatchArgs &a, bool comp, int block, hipStream_t s)
 {
     return with_bool(comp, [&](auto CP) {
-        const int64_t np = a.n_packed_items, ng = a.n_gemv_items - np, nd = a.n_items - a.n_gemv_items;
-        if (np > 0)
-            hipLaunchKernelGGL((k_grouped_gemv<T, CP.value>), dim3((unsigned)np), dim3(block), 0, s, a);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess)
-            return e;
-        if (ng > 0)
-            hipLaunchKernelGGL((k_grouped_gemv_scalar<T, CP.value>), dim3((unsigned)ng), dim3(block), 0, s, a);
-        e = hipGetLastError();
-        if (e != hipSuccess || nd <= 0)
-            return e;
-        hipLaunchKernelGGL((k_grouped_dot<T, CP.value>), dim3((unsigned)nd), dim3(block), 0, s, a);
+        hipLaunchKernelGGL((k_grouped<T, CP.value>), dim3((unsigned)a.n_items), dim3(block), 0, s, a);
         return hipGetLastError();
     });
 }
@@ -461,7 +453,7 @@ hipError_t launch_batch_finalize(const BatchDot *dots, int64_t nd, const double 
 {
     if (nd <= 0)
         return hipSuccess;
-    const int64_t blocks = (nd + 255) / 256;
+    const int64_t blocks = (nd + 3) / 4;
     return with_bool(comp, [&](auto CP) {
         hipLaunchKernelGGL((k_batch_finalize<CP.value>), dim3((unsigned)blocks), dim3(256), 0, s, dots, nd,
                            (const DD *)partials, out_f64);

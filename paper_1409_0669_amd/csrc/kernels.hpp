@@ -199,8 +199,6 @@ struct BatchDot {
 struct BatchArgs {
     const BatchItem *items;
     int64_t n_items;
-    int64_t n_gemv_items;   // grouped launch: items[0, n_gemv_items) are GEMV tiles, the rest dot chunks
-    int64_t n_packed_items; // grouped launch: of those, items[0, n_packed_items) are read in packs
     const BatchGemv *gemv;
     const BatchDot *dots;
     double *partials;       // 2 doubles per dot chunk
