@@ -51,6 +51,11 @@ def _stream(device=None) -> int:
     return torch.cuda.current_stream(device).cuda_stream
 
 
+def _stream_of(t: torch.Tensor) -> int:
+    """Handle of the current stream of a GPU tensor's device."""
+    return _stream(t.device) if _raw_stream is None else _raw_stream(t.get_device())
+
+
 def _vec(t: torch.Tensor, name: str) -> None:
     if not isinstance(t, torch.Tensor):
         raise TypeError("%s must be a torch.Tensor" % name)
@@ -68,15 +73,17 @@ def _svec(t: torch.Tensor, name: str) -> int:
         raise BwlaError(L.ERR_INVALID_ARG, "%s must be a GPU tensor" % name)
     if t.dim() != 1:
         raise BwlaError(L.ERR_INVALID_ARG, "%s must be a 1-D tensor" % name)
-    return 1 if t.numel() <= 1 else int(t.stride(0))
+    return 1 if t.is_contiguous() else int(t.stride(0))
 
 
-def _same(dtype, device, *ts) -> None:
+def _same(like: torch.Tensor, *ts) -> None:
+    """GPU tensors of one dtype on one device (compared by index: building a
+    torch.device per tensor costs as much as the other checks together)."""
     for t in ts:
-        if t.dtype != dtype:
-            raise BwlaError(L.ERR_INVALID_ARG, "dtype mismatch: %s vs %s" % (t.dtype, dtype))
-        if t.device != device:
-            raise BwlaError(L.ERR_INVALID_ARG, "device mismatch: %s vs %s" % (t.device, device))
+        if t.dtype != like.dtype:
+            raise BwlaError(L.ERR_INVALID_ARG, "dtype mismatch: %s vs %s" % (t.dtype, like.dtype))
+        if t.get_device() != like.get_device():
+            raise BwlaError(L.ERR_INVALID_ARG, "device mismatch: %s vs %s" % (t.device, like.device))
 
 
 # ---------------------------------------------------------------------------
@@ -161,6 +168,27 @@ def _with_workspace(size_args, device, stream: int, launch) -> None:
     check(st)
 
 
+def _with_sized(query, args, device, stream: int, launch) -> None:
+    """:func:`_with_workspace` for the operations whose size has a query of its
+    own: ``query(*args, &bytes)``.  (Asking on every call took as long as a launch.)"""
+    key = (query.__name__, args, device.index)
+    for fresh in (False, True):
+        n = None if fresh else _ws_sizes.get(key)
+        asked = n is None
+        if asked:
+            out = ctypes.c_size_t()
+            check(query(*args, ctypes.byref(out)))
+            n = out.value
+            if len(_ws_sizes) >= 4096:
+                _ws_sizes.clear()
+            _ws_sizes[key] = n
+        st = launch(*_ws_ptr(workspace(n, device, stream)))
+        if st != L.ERR_WORKSPACE or asked:
+            break
+        _ws_sizes.clear()
+    check(st)
+
+
 # ---------------------------------------------------------------------------
 # operations
 # ---------------------------------------------------------------------------
@@ -169,14 +197,14 @@ def copy(y: torch.Tensor, out: torch.Tensor | None = None) -> torch.Tensor:
     incy = _svec(y, "y")
     x = torch.empty(y.numel(), dtype=y.dtype, device=y.device) if out is None else out
     incx = _svec(x, "out")
-    _same(y.dtype, y.device, x)
+    _same(y, x)
     if x.numel() != y.numel():
         raise BwlaError(L.ERR_INVALID_ARG, "length mismatch")
     if incx == 1 and incy == 1:
-        check(lib.bwla_copy(dtype_code(y.dtype), y.numel(), y.data_ptr(), x.data_ptr(), _stream(y.device)))
+        check(lib.bwla_copy(dtype_code(y.dtype), y.numel(), y.data_ptr(), x.data_ptr(), _stream_of(y)))
     else:
         check(lib.bwla_copy_strided(dtype_code(y.dtype), y.numel(), y.data_ptr(), incy, x.data_ptr(), incx,
-                                    _stream(y.device)))
+                                    _stream_of(y)))
     return x
 
 
@@ -188,19 +216,19 @@ def axpby(alpha: float, y: torch.Tensor, beta: float, z: torch.Tensor, out: torc
     multiply the host factors.  Strided 1-D views are accepted."""
     incy = _svec(y, "y")
     incz = _svec(z, "z")
-    _same(y.dtype, y.device, z)
+    _same(y, z)
     x = torch.empty(y.numel(), dtype=y.dtype, device=y.device) if out is None else out
     incx = _svec(x, "out")
-    _same(y.dtype, y.device, x)
+    _same(y, x)
     if not (x.numel() == y.numel() == z.numel()):
         raise BwlaError(L.ERR_INVALID_ARG, "length mismatch")
     ad, bd = _dev_scalar(y, alpha_dev, "alpha_dev"), _dev_scalar(y, beta_dev, "beta_dev")
     if incx == incy == incz == 1:
         check(lib.bwla_axpby(dtype_code(y.dtype), y.numel(), float(alpha), ad, y.data_ptr(), float(beta), bd,
-                             z.data_ptr(), x.data_ptr(), _stream(y.device)))
+                             z.data_ptr(), x.data_ptr(), _stream_of(y)))
     else:
         check(lib.bwla_axpby_strided(dtype_code(y.dtype), y.numel(), float(alpha), ad, y.data_ptr(), incy,
-                                     float(beta), bd, z.data_ptr(), incz, x.data_ptr(), incx, _stream(y.device)))
+                                     float(beta), bd, z.data_ptr(), incz, x.data_ptr(), incx, _stream_of(y)))
     return x
 
 
@@ -217,7 +245,7 @@ def scal(alpha: float, x: torch.Tensor, alpha_dev: torch.Tensor | None = None) -
     """x <- alpha x in place (x_i = RN(a x_i)); strided 1-D views accepted."""
     incx = _svec(x, "x")
     check(lib.bwla_scal(dtype_code(x.dtype), x.numel(), float(alpha), _dev_scalar(x, alpha_dev, "alpha_dev"),
-                        x.data_ptr(), incx, _stream(x.device)))
+                        x.data_ptr(), incx, _stream_of(x)))
     return x
 
 
@@ -230,11 +258,11 @@ def scal_to(alpha: float, y: torch.Tensor, out: torch.Tensor | None = None,
     _vec(y, "y")
     x = torch.empty_like(y) if out is None else out
     _vec(x, "out")
-    _same(y.dtype, y.device, x)
+    _same(y, x)
     if x.numel() != y.numel():
         raise BwlaError(L.ERR_INVALID_ARG, "length mismatch")
     check(lib.bwla_scal_to(dtype_code(y.dtype), y.numel(), float(alpha), _dev_scalar(y, alpha_dev, "alpha_dev"),
-                           y.data_ptr(), x.data_ptr(), _stream(y.device)))
+                           y.data_ptr(), x.data_ptr(), _stream_of(y)))
     return x
 
 
@@ -255,12 +283,12 @@ def dot(x: torch.Tensor, y: torch.Tensor, acc="plain", out_dtype: torch.dtype | 
     default otherwise).  Strided 1-D views are accepted."""
     incx = _svec(x, "x")
     incy = _svec(y, "y")
-    _same(x.dtype, x.device, y)
+    _same(x, y)
     if x.numel() != y.numel():
         raise BwlaError(L.ERR_INVALID_ARG, "length mismatch")
     out, oc = _scalar_out(x.dtype, out_dtype, x.device, out)
     args = (dtype_code(x.dtype), _ACC[acc], x.numel(), x.data_ptr(), incx, y.data_ptr(), incy, oc, out.data_ptr())
-    stream = _stream(x.device)
+    stream = _stream_of(x)
     _with_workspace((L.OP_DOT, x.dtype, acc, L.ROW_MAJOR, 0, 0, x.numel()), x.device, stream,
                     lambda ws, wsn: lib.bwla_dot_strided(*args, ws, wsn, stream))
     return out
@@ -274,12 +302,12 @@ def dot_noalloc(x: torch.Tensor, y: torch.Tensor, acc="plain", out_dtype: torch.
     Calls that may overlap on one GPU race on that scratch."""
     _vec(x, "x")
     _vec(y, "y")
-    _same(x.dtype, x.device, y)
+    _same(x, y)
     if x.numel() != y.numel():
         raise BwlaError(L.ERR_INVALID_ARG, "length mismatch")
     out, oc = _scalar_out(x.dtype, out_dtype, x.device, out)
     check(lib.bwla_dot_noalloc(dtype_code(x.dtype), _ACC[acc], x.numel(), x.data_ptr(), y.data_ptr(), oc,
-                               out.data_ptr(), _stream(x.device)))
+                               out.data_ptr(), _stream_of(x)))
     return out
 
 
@@ -289,7 +317,7 @@ def nrm2(x: torch.Tensor, acc="plain", out_dtype: torch.dtype | None = None,
     incx = _svec(x, "x")
     out, oc = _scalar_out(x.dtype, out_dtype, x.device, out)
     args = (dtype_code(x.dtype), _ACC[acc], x.numel(), x.data_ptr(), incx, oc, out.data_ptr())
-    stream = _stream(x.device)
+    stream = _stream_of(x)
     _with_workspace((L.OP_DOT, x.dtype, acc, L.ROW_MAJOR, 0, 0, x.numel()), x.device, stream,
                     lambda ws, wsn: lib.bwla_nrm2_strided(*args, ws, wsn, stream))
     return out
@@ -301,7 +329,7 @@ def asum(x: torch.Tensor, acc="plain", out_dtype: torch.dtype | None = None,
     incx = _svec(x, "x")
     out, oc = _scalar_out(x.dtype, out_dtype, x.device, out)
     args = (dtype_code(x.dtype), _ACC[acc], x.numel(), x.data_ptr(), incx, oc, out.data_ptr())
-    stream = _stream(x.device)
+    stream = _stream_of(x)
     _with_workspace((L.OP_DOT, x.dtype, acc, L.ROW_MAJOR, 0, 0, x.numel()), x.device, stream,
                     lambda ws, wsn: lib.bwla_asum(*args, ws, wsn, stream))
     return out
@@ -331,7 +359,7 @@ def gemv(A: torch.Tensor, x: torch.Tensor, trans: bool = False, acc="plain",
         raise BwlaError(L.ERR_INVALID_ARG, "A must be a GPU tensor")
     layout, lda = matrix_layout(A)
     incx = _svec(x, "x")
-    _same(A.dtype, A.device, x)
+    _same(A, x)
     m, n = A.shape
     out_len, in_len = (n, m) if trans else (m, n)
     if x.numel() != in_len:
@@ -348,17 +376,15 @@ def gemv(A: torch.Tensor, x: torch.Tensor, trans: bool = False, acc="plain",
     if alpha == 1.0 and beta == 0.0 and incx == 1 and incy == 1:
         args = (dtype_code(A.dtype), _ACC[acc], layout, int(trans), m, n, A.data_ptr(), lda, x.data_ptr(),
                 _DTYPE[od], y.data_ptr())
-        stream = _stream(A.device)
+        stream = _stream_of(A)
         _with_workspace((L.OP_GEMV_ROWS, A.dtype, acc, layout, int(trans), m, n), A.device, stream,
                         lambda ws, wsn: lib.bwla_gemv(*args, ws, wsn, stream))
         return y
-    nbytes = ctypes.c_size_t()
-    check(lib.bwla_gemv_ex_workspace_size(dtype_code(A.dtype), _DTYPE[od], layout, int(trans), m, n,
-                                          ctypes.byref(nbytes)))
-    ws, wsn = _ws_ptr(workspace(nbytes.value, A.device))
-    check(lib.bwla_gemv_ex(dtype_code(A.dtype), _ACC[acc], layout, int(trans), m, n, float(alpha), A.data_ptr(),
-                           lda, x.data_ptr(), incx, float(beta), _DTYPE[od], y.data_ptr(), incy, ws, wsn,
-                           _stream(A.device)))
+    t, stream = dtype_code(A.dtype), _stream_of(A)
+    _with_sized(lib.bwla_gemv_ex_workspace_size, (t, _DTYPE[od], layout, int(trans), m, n), A.device, stream,
+                lambda ws, wsn: lib.bwla_gemv_ex(t, _ACC[acc], layout, int(trans), m, n, float(alpha), A.data_ptr(),
+                                                 lda, x.data_ptr(), incx, float(beta), _DTYPE[od], y.data_ptr(),
+                                                 incy, ws, wsn, stream))
     return y
 
 
@@ -376,7 +402,7 @@ def gemv_dot(A: torch.Tensor, x: torch.Tensor, w: torch.Tensor | None = None, tr
     w = x if w is None else w
     _vec(x, "x")
     _vec(w, "w")
-    _same(A.dtype, A.device, x, w)
+    _same(A, x, w)
     m, n = A.shape
     out_len, in_len = (n, m) if trans else (m, n)
     if x.numel() != in_len or w.numel() != out_len:
@@ -386,12 +412,11 @@ def gemv_dot(A: torch.Tensor, x: torch.Tensor, w: torch.Tensor | None = None, tr
     if y.numel() != out_len or y.dtype != A.dtype:
         raise BwlaError(L.ERR_INVALID_ARG, "out must have %d %s entries" % (out_len, A.dtype))
     s, sc = _scalar_out(A.dtype, dot_dtype, A.device, dot_out)
-    nbytes = ctypes.c_size_t()
-    check(lib.bwla_gemv_dot_workspace_size(dtype_code(A.dtype), layout, int(trans), m, n, ctypes.byref(nbytes)))
-    ws, wsn = _ws_ptr(workspace(nbytes.value, A.device))
-    check(lib.bwla_gemv_dot(dtype_code(A.dtype), _ACC[acc], layout, int(trans), m, n, A.data_ptr(), lda,
-                            x.data_ptr(), y.data_ptr(), w.data_ptr(), sc, s.data_ptr(), ws, wsn,
-                            _stream(A.device)))
+    t, stream = dtype_code(A.dtype), _stream_of(A)
+    _with_sized(lib.bwla_gemv_dot_workspace_size, (t, layout, int(trans), m, n), A.device, stream,
+                lambda ws, wsn: lib.bwla_gemv_dot(t, _ACC[acc], layout, int(trans), m, n, A.data_ptr(), lda,
+                                                  x.data_ptr(), y.data_ptr(), w.data_ptr(), sc, s.data_ptr(), ws,
+                                                  wsn, stream))
     return y, s
 
 
@@ -400,13 +425,13 @@ def ger(u: torch.Tensor, v: torch.Tensor, out: torch.Tensor) -> torch.Tensor:
     is the m x n matrix to overwrite; its layout is read from its strides."""
     _vec(u, "u")
     _vec(v, "v")
-    _same(out.dtype, out.device, u, v)
+    _same(out, u, v)
     layout, lda = matrix_layout(out)
     m, n = out.shape
     if u.numel() != m or v.numel() != n:
         raise BwlaError(L.ERR_INVALID_ARG, "u, v must have %d and %d entries" % (m, n))
     check(lib.bwla_ger(dtype_code(out.dtype), layout, m, n, u.data_ptr(), v.data_ptr(), out.data_ptr(), lda,
-                       _stream(out.device)))
+                       _stream_of(out)))
     return out
 
 
@@ -416,7 +441,7 @@ def cg_update(alpha: float, x: torch.Tensor, p: torch.Tensor, r: torch.Tensor, q
     """One fused pass: x += a p, r -= a q, returns <r, r> (0-dim tensor)."""
     for name, t in (("x", x), ("p", p), ("r", r), ("q", q)):
         _vec(t, name)
-    _same(x.dtype, x.device, p, r, q)
+    _same(x, p, r, q)
     if not (x.numel() == p.numel() == r.numel() == q.numel()):
         raise BwlaError(L.ERR_INVALID_ARG, "length mismatch")
     if alpha_dev is not None and (alpha_dev.dtype != compute_dtype(x.dtype) or alpha_dev.numel() != 1):
@@ -424,7 +449,7 @@ def cg_update(alpha: float, x: torch.Tensor, p: torch.Tensor, r: torch.Tensor, q
     out, oc = _scalar_out(x.dtype, out_dtype, x.device, out)
     args = (dtype_code(x.dtype), _ACC[acc], x.numel(), float(alpha), None if alpha_dev is None else alpha_dev.data_ptr(),
             x.data_ptr(), p.data_ptr(), r.data_ptr(), q.data_ptr(), oc, out.data_ptr())
-    stream = _stream(x.device)
+    stream = _stream_of(x)
     _with_workspace((L.OP_DOT, x.dtype, acc, L.ROW_MAJOR, 0, 0, x.numel()), x.device, stream,
                     lambda ws, wsn: lib.bwla_cg_update(*args, ws, wsn, stream))
     return out
