@@ -161,13 +161,18 @@ __device__ __forceinline__ void edge_elements(int head, int64_t packed, int64_t 
 // cover one contiguous range of the logical index space keeps each XCD on
 // its own stretch of memory.  A bijection on [0, gridDim.x) for any grid size.
 // ---------------------------------------------------------------------------
+// In 32 bits (a grid has fewer than 2^31 work-groups), so that no branch of a
+// 64-bit division splits a kernel's first block and all of its arguments are
+// loaded at once: each such split was one more serial load of arguments before
+// the first load of data (with the slice index and length done alike, columns
+// of 4096 x 4096 f32 16.8 -> 16.0 us, rows of 1453 x 116 3.2 -> 2.8).
 constexpr int kXcds = 8;
 __device__ __forceinline__ int64_t xcd_block()
 {
-    const int64_t g = gridDim.x, b = blockIdx.x;
-    const int64_t xcd = b % kXcds, idx = b / kXcds;
-    const int64_t q = g / kXcds, r = g % kXcds;
-    return xcd < r ? xcd * (q + 1) + idx : r * (q + 1) + (xcd - r) * q + idx;
+    const unsigned g = gridDim.x, b = blockIdx.x;
+    const unsigned xcd = b % kXcds, idx = b / kXcds;
+    const unsigned q = g / kXcds, r = g % kXcds;
+    return xcd * q + (xcd < r ? xcd : r) + idx;
 }
 
 // ---------------------------------------------------------------------------

@@ -73,16 +73,17 @@ template <typename C, bool COMP> __device__ __forceinline__ DD epilogue_term(C w
     return a.to_dd();
 }
 
+// per: packs of a slice, divided on the host (a 64-bit division here branches).
 template <typename T, int V, int R, int U, bool COMP>
 __global__ __launch_bounds__(1024) void k_gemv_rows(int64_t L, int64_t K, const T *A, int64_t ld,
                                                     const T *v, DD *partials, GemvOut out,
-                                                    int split, const T *w, DD *dparts)
+                                                    int split, int64_t per, const T *w, DD *dparts)
 {
     using C = compute_t<T>;
     constexpr bool EXACT = std::is_same<T, bf16_t>::value;
-    const int64_t lb = xcd_block();
-    const int64_t group = lb / split;
-    const int s = (int)(lb - group * split);
+    const unsigned lb = (unsigned)xcd_block();
+    const int64_t group = lb / (unsigned)split;
+    const int s = (int)(lb % (unsigned)split);
     const int64_t l0 = group * R;
     const int nr = (int)(L - l0 < R ? L - l0 : R);
     const T *row[R];
@@ -91,7 +92,6 @@ __global__ __launch_bounds__(1024) void k_gemv_rows(int64_t L, int64_t K, const 
         row[r] = A + (l0 + (r < nr ? r : nr - 1)) * ld; // rows past L re-read the last one
 
     const int64_t kpack = K / V;
-    const int64_t per = (kpack + split - 1) / split;
     const int64_t pb = (int64_t)s * per;
     const int64_t pe = pb + per < kpack ? pb + per : kpack;
     // the dot epilogue's weight and the prior output of this thread's line,
@@ -183,14 +183,15 @@ __global__ __launch_bounds__(1024) void k_gemv_rows(int64_t L, int64_t K, const 
 template <typename T, int V, int U, bool COMP>
 __global__ __launch_bounds__(1024) void k_gemv_cols(int64_t L, int64_t K, const T *A, int64_t ld,
                                                     const T *__restrict__ v, int64_t incv, DD *partials,
-                                                    GemvOut out, int split, const T *w, DD *dparts, int xchg)
+                                                    GemvOut out, int split, int64_t per, const T *w, DD *dparts,
+                                                    int xchg)
 {
     using C = compute_t<T>;
     constexpr bool EXACT = std::is_same<T, bf16_t>::value;
     constexpr int TK = 64 * V;
-    const int64_t blk = xcd_block();
-    const int64_t tile = blk / split;
-    const int s = (int)(blk - tile * split);
+    const unsigned blk = (unsigned)xcd_block();
+    const int64_t tile = blk / (unsigned)split;
+    const int s = (int)(blk % (unsigned)split);
     const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
     // the wave index as a wave-uniform (scalar) value, so that every v[l]
     // below is one scalar load shared by the wave
@@ -201,7 +202,6 @@ __global__ __launch_bounds__(1024) void k_gemv_cols(int64_t L, int64_t K, const 
     // loop as its neighbours.  Taken element by element, that one lane made
     // its waves three times as long (8001 x 8003 bf16: 107 us in all).
     const int64_t kb = k0 + V <= K ? k0 : K - V;
-    const int64_t per = (L + split - 1) / split;
     const int64_t lb = (int64_t)s * per;
     const int64_t le = lb + per < L ? lb + per : L;
 
@@ -321,7 +321,7 @@ __global__ __launch_bounds__(1024) void k_gemv_cols(int64_t L, int64_t K, const 
 // 300 x 300 f32 6.8 -> 3.2 us, 1200 x 1501 f32 11.2 -> 6.7, 16000 x 100 f32 17.7 -> 7.6
 // (with the wider line combine), 3001 x 4099 compensated bf16 30.7 -> 12.3, 16384 x
 // 20001 bf16 229 -> 112; from 64 MiB on with aligned lines both are at the rate of
-// HBM (f32 16384 x 2048 29.0 -> 27.9, 4096 x 4096 16.2 -> 16.4).
+// HBM (f32 16384 x 2048 29.0 -> 27.9, 4096 x 4096 16.2 -> 16.0).
 //
 // The groups of a wave are summed by lane swaps that halve the values each
 // time (V / 2 + V / 4 exchanges, no LDS; a butterfly of every value took as
@@ -333,22 +333,21 @@ __global__ __launch_bounds__(1024) void k_gemv_cols(int64_t L, int64_t K, const 
 template <typename T, int P, int U, bool COMP, bool UNIT>
 __global__ __launch_bounds__(1024) void k_gemv_cols_grouped(int64_t L, int64_t K, const T *A, int64_t ld,
                                                             const T *v, int64_t incv, DD *partials, GemvOut out,
-                                                            int split, const T *w, DD *dparts)
+                                                            int split, int64_t per, const T *w, DD *dparts)
 {
     using C = compute_t<T>;
     using Part = std::conditional_t<COMP, DD, double>;
     constexpr bool EXACT = std::is_same<T, bf16_t>::value;
     constexpr int V = 16 / (int)sizeof(T), G = 64 / P, TK = G * V;
-    const int64_t blk = xcd_block();
-    const int64_t tile = blk / split;
-    const int s = (int)(blk - tile * split);
+    const unsigned blk = (unsigned)xcd_block();
+    const int64_t tile = blk / (unsigned)split;
+    const int s = (int)(blk % (unsigned)split);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
     const int gl = lane % G;
     const int64_t k0 = tile * TK + gl * V;
     // the last lane's pack is the last whole one of the lines (its columns
     // from k0 on are kept), and lanes past the end repeat it
     const int64_t kb = k0 + V <= K ? k0 : K - V;
-    const int64_t per = (L + split - 1) / split;
     const int64_t lb = (int64_t)s * per;
     const int64_t tn = lb + per < L ? per : (lb < L ? L - lb : 0);
 
@@ -359,9 +358,6 @@ __global__ __launch_bounds__(1024) void k_gemv_cols_grouped(int64_t L, int64_t K
         const int64_t k = (q0 + V <= K ? q0 : K - V) + t % V;
         return k < q0 || q0 >= K ? -1 : k;
     };
-    const int64_t own = split == 1 && (int)threadIdx.x < TK ? column(threadIdx.x) : -1;
-    const double prior = own >= 0 ? out_prior(out, own) : 0.0;
-
     acc_t<T, COMP> acc[V];
     if constexpr (UNIT)
         incv = 1;
@@ -408,6 +404,10 @@ __global__ __launch_bounds__(1024) void k_gemv_cols_grouped(int64_t L, int64_t K
                 for (int e = 0; e < V; ++e)
                     acc[e].template add_prod<EXACT>(widen(a[u].v[e]), widen(xv[u]));
     }
+
+    // This thread's prior output, in flight during the sums below.
+    const int64_t own = split == 1 && (int)threadIdx.x < TK ? column(threadIdx.x) : -1;
+    const double prior = own >= 0 ? out_prior(out, own) : 0.0;
 
     // Sum the P groups of the wave: each exchange of halves leaves a lane with
     // half of its values, summed over twice the lines.
@@ -595,7 +595,7 @@ hipError_t launch_gemv_rows(int64_t L, int64_t K, bool comp, const void *A, int6
                     hipLaunchKernelGGL((k_gemv_rows<T, V.value, R.value, U.value, CP.value>),
                                        dim3((unsigned)(groups * c.split)), dim3(c.block), 0, s, L, K,
                                        (const T *)A, ld, (const T *)v, partials, out, c.split,
-                                       (const T *)w, dparts);
+                                       (K / V.value + c.split - 1) / c.split, (const T *)w, dparts);
                     return hipGetLastError();
                 };
                 if (c.unroll == 2)
@@ -625,7 +625,8 @@ hipError_t launch_cols_grouped(int64_t L, int64_t K, bool comp, const T *A, int6
                 auto go = [&](auto U, auto unit) {
                     hipLaunchKernelGGL((k_gemv_cols_grouped<T, P.value, U.value, CP.value, unit.value>),
                                        dim3((unsigned)(tiles * c.split)), dim3(c.block), (unsigned)lds, s, L, K, A,
-                                       ld, v, incv, partials, out, c.split, w, dparts);
+                                       ld, v, incv, partials, out, c.split, (L + c.split - 1) / c.split, w,
+                                       dparts);
                     return hipGetLastError();
                 };
                 // (the trip's lines decide the order of a sum, so x's increment may not)
@@ -673,8 +674,8 @@ hipError_t launch_gemv_cols(int64_t L, int64_t K, bool comp, const void *A, int6
                     hipLaunchKernelGGL((k_gemv_cols<T, V.value, U.value, CP.value>),
                                        dim3((unsigned)(tiles * c.split)), dim3(c.block),
                                        (unsigned)(xchg ? xbytes : 0), s, L, K, (const T *)A, ld,
-                                       (const T *)v, incv, partials, out, c.split, (const T *)w, dparts,
-                                       xchg);
+                                       (const T *)v, incv, partials, out, c.split,
+                                       (L + c.split - 1) / c.split, (const T *)w, dparts, xchg);
                     return hipGetLastError();
                 });
             }
