@@ -430,9 +430,8 @@ def _replay_ms(torch, g, reps):
 
 
 def batched_rows(torch, W, ops, reps):
-    """The uneven batch three ways: the batched plan (one launch per kind of
-    work item, one work-group per item) launched directly and replayed from its HIP
-    graph, and -- as the baseline it replaces -- one library call per problem,
+    """The uneven batch three ways: the batched plan (one launch, one
+    work-group per work item) launched directly and replayed from its HIP graph, and -- as the baseline it replaces -- one library call per problem,
     all captured in one HIP graph."""
     from paper_1409_0669_amd.batch import BatchPlan
     out = {}

@@ -14,8 +14,8 @@ Submodules (imported on first use; importing them fails loudly when
 * ``ops``       tensor-level calls (copy, axpby, scal, dot, nrm2, asum, gemv,
                 gemv_dot, ger, cg_update)
 * ``autograd``  ``GemvFn`` and ``DotFn`` with hand-written backward kernels
-* ``batch``     ``BatchPlan``: many uneven GEMVs and dots, one launch per kind of
-                work item, replayable from a HIP graph
+* ``batch``     ``BatchPlan``: many uneven GEMVs and dots in one launch,
+                replayable from a HIP graph
 * ``tune``      the autotuner and the configuration-space study
 * ``build``     compiles the library with hipcc
 """

@@ -1,10 +1,10 @@
 // batched.hip -- many uneven row-major GEMVs and dots, batched.
 //
-// Two designs share the work-item list.  The grouped launch (k_grouped_gemv
-// and k_grouped_dot, below the persistent kernel) runs one work-group per
-// item; it is the one plans use.  The persistent kernel (k_batched) keeps a
-// grid sized to the machine busy from an atomic work queue; it has not been
-// validated on hardware and plan creation refuses it (see api.cpp).
+// Two designs share the work-item list.  The grouped launch (k_grouped, below
+// the persistent kernel) runs one work-group per item; it is the one plans
+// use.  The persistent kernel (k_batched) keeps a grid sized to the machine
+// busy from an atomic work queue; it has not been validated on hardware and
+// plan creation refuses it (see api.cpp).
 //
 // The host flattens every problem into work items -- row tiles of a GEMV
 // (full row length) and fixed-size chunks of a dot -- ordered by decreasing
@@ -18,7 +18,7 @@
 // inside the group.  A dot chunk is reduced across the wave; a single-chunk
 // dot writes its result directly, otherwise the chunk's float64 partial goes
 // to a slot of the dot and a small finalize kernel combines each dot's slots
-// in chunk order.  Every result depends only on its own problem's sizes, never
+// in a fixed order.  Every result depends only on its own problem's sizes, never
 // on the batch order or on which wave ran which item.
 #include "device.hpp"
 #include "kernels.hpp"

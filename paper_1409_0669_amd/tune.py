@@ -214,7 +214,7 @@ class Workload:
 
     def time(self, reps: int) -> float:
         """ms per call.  A batch plan (about a millisecond of GPU work in
-        four launches) is timed as a single run on an idle stream, as the
+        two launches) is timed as a single run on an idle stream, as the
         benchmark times it; behind the blocker, four runs back to back ranked
         its configurations differently from single runs."""
         if self.op == "batch":
