@@ -324,7 +324,11 @@ bwla_status bwla_workspace_size(bwla_op op, bwla_dtype t, bwla_acc acc, bwla_lay
  * run in one launch with one work-group per item (the hardware dispatcher
  * hands them out in order).  Each dot's chunk partials are combined in a fixed
  * order by a finalize kernel, where a dot has more than one, so results do
- * not depend on the batch order or on scheduling.
+ * not depend on the batch order or on scheduling.  A plan in which a problem
+ * writes what one of another kind reads or writes (a dot of a GEMV's y) runs
+ * in up to three launches: GEMVs whose row fits 32 KiB in the compute
+ * precision, longer ones, dots.  Problems of one kind must not depend on each
+ * other.
  * create: copies the descriptors to the device and allocates the plan's own
  *         counters and partial slots (the only allocating call; not allowed
  *         while `stream` capture is active).

@@ -1515,6 +1515,7 @@ struct bwla_batch_plan {
     int grid = 0, block = 256, vec = 1;
     int64_t n_items = 0, n_dots = 0;
     bool finalize = false; // a dot has more than one chunk
+    std::vector<int64_t> launches; // items of each launch
     double bytes = 0;
     BatchItem *d_items = nullptr;
     BatchGemv *d_gemv = nullptr;
@@ -1553,6 +1554,35 @@ bool persistent_requested()
     return v && v[0] == '1';
 }
 
+// Memory that a problem of a batch reads or writes.  Kinds in the order in
+// which a plan's dependent problems run: GEMVs with rows of up to
+// kShortRowBytes (in the compute precision), longer ones, dots.
+struct Touch {
+    uintptr_t lo, hi;
+    int kind;
+    bool write;
+};
+constexpr int kKinds = 3;
+
+// GEMVs that ran first when each kind had a launch of its own.
+bool short_rows(int64_t n, size_t es) { return n <= 32768 / (es == 8 ? 8 : 4) - 64 * (16 / (int64_t)es); }
+
+// True when a problem writes what one of another kind reads or writes.  One
+// sweep over the spans by their starts: an earlier one that ends past this
+// one's start overlaps it.
+bool kinds_depend(std::vector<Touch> &t)
+{
+    std::sort(t.begin(), t.end(), [](const Touch &a, const Touch &b) { return a.lo < b.lo; });
+    uintptr_t end[kKinds][2] = {}; // furthest end so far, of reads and of writes
+    for (const Touch &x : t) {
+        for (int k = 0; k < kKinds; ++k)
+            if (k != x.kind && (end[k][1] > x.lo || (x.write && end[k][0] > x.lo)))
+                return true;
+        end[x.kind][x.write] = std::max(end[x.kind][x.write], x.hi);
+    }
+    return false;
+}
+
 hipError_t enqueue_batch(bwla_batch_plan *p, hipStream_t s)
 {
     hipError_t e = hipSuccess;
@@ -1576,7 +1606,13 @@ hipError_t enqueue_batch(bwla_batch_plan *p, hipStream_t s)
         using T = std::remove_pointer_t<decltype(tag)>;
         if (p->persistent)
             return launch_batched<T>(a, p->acc == BWLA_ACC_COMPENSATED, p->grid, p->block, s);
-        return launch_grouped<T>(a, p->acc == BWLA_ACC_COMPENSATED, p->block, s);
+        hipError_t r = hipSuccess;
+        for (size_t i = 0; i < p->launches.size() && r == hipSuccess; ++i) {
+            a.n_items = p->launches[i];
+            r = launch_grouped<T>(a, p->acc == BWLA_ACC_COMPENSATED, p->block, s);
+            a.items += a.n_items;
+        }
+        return r;
     });
     if (e != hipSuccess || !p->finalize)
         return e;
@@ -1613,6 +1649,11 @@ bwla_status bwla_batch_plan_create(bwla_dtype t, bwla_acc acc, bwla_dtype out_t,
     const size_t es = dsize(t), os = out_t == BWLA_F64 ? 8 : 4;
     bool aligned = true;
     const int nv = native_vec(t);
+    std::vector<Touch> touched;
+    auto touch = [&](Span m, int kind, bool write) {
+        if (m.hi > m.lo)
+            touched.push_back({m.lo, m.hi, kind, write});
+    };
     for (int i = 0; i < ng; ++i) {
         const bwla_gemv_desc &q = g[i];
         if (q.m < 0 || q.n < 0 || q.lda < std::max<int64_t>(1, q.n))
@@ -1627,7 +1668,10 @@ bwla_status bwla_batch_plan_create(bwla_dtype t, bwla_acc acc, bwla_dtype out_t,
                 return fail(BWLA_ERR_INVALID_ARG, "gemv %d: y overlaps A or x", i);
             if (fit_vec(nv, es, {q.A, q.x}) != nv)
                 aligned = false;
+            touch(span(q.A, matrix_bytes(q.m, q.n, q.lda, es)), short_rows(q.n, es) ? 0 : 1, false);
+            touch(span(q.x, q.n * es), short_rows(q.n, es) ? 0 : 1, false);
         }
+        touch(span(q.y, q.m * os), short_rows(q.n, es) ? 0 : 1, true);
     }
     for (int i = 0; i < nd; ++i) {
         const bwla_dot_desc &q = d[i];
@@ -1639,8 +1683,15 @@ bwla_status bwla_batch_plan_create(bwla_dtype t, bwla_acc acc, bwla_dtype out_t,
                 return fail(BWLA_ERR_INVALID_ARG, "dot %d: out overlaps an input", i);
             if (fit_vec(nv, es, {q.x, q.y}) != nv)
                 aligned = false;
+            touch(span(q.x, q.n * es), 2, false);
+            touch(span(q.y, q.n * es), 2, false);
         }
+        touch(span(q.out, os), 2, true);
     }
+    // A plan may chain its problems by kind, a dot of a GEMV's result for
+    // one: then each kind has a launch of its own.  Independent problems,
+    // the usual ones, run in one launch.
+    const bool dependent = kinds_depend(touched);
     // the plan's algorithmic bytes select its table entry (a cfg field that
     // is set overrides it)
     double total = 0;
@@ -1663,6 +1714,7 @@ bwla_status bwla_batch_plan_create(bwla_dtype t, bwla_acc acc, bwla_dtype out_t,
     struct Work {
         BatchItem it;
         double cost;
+        int phase; // launch
     };
     std::vector<Work> work;
     std::vector<BatchGemv> hg(ng);
@@ -1720,6 +1772,7 @@ bwla_status bwla_batch_plan_create(bwla_dtype t, bwla_acc acc, bwla_dtype out_t,
             w.it.begin = r0;
             w.it.end = std::min(q.m, r0 + rpi);
             w.cost = (double)(w.it.end - w.it.begin) * std::max<int64_t>(q.n, 1) * es;
+            w.phase = dependent && !short_rows(q.n, es);
             work.push_back(w);
         }
         p->bytes += (double)q.m * q.n * es + (double)q.n * es + (double)q.m * os;
@@ -1746,6 +1799,7 @@ bwla_status bwla_batch_plan_create(bwla_dtype t, bwla_acc acc, bwla_dtype out_t,
             w.it.end = std::min<int64_t>(q.n, (int64_t)(c + 1) * kChunk);
             w.it.chunk = c;
             w.cost = (double)std::max<int64_t>(1, w.it.end - w.it.begin) * 2 * es;
+            w.phase = dependent ? 2 : 0;
             work.push_back(w);
         }
         slots += b.chunks;
@@ -1757,10 +1811,17 @@ bwla_status bwla_batch_plan_create(bwla_dtype t, bwla_acc acc, bwla_dtype out_t,
         std::stable_sort(work.begin(), work.end(), [](const Work &a, const Work &b) { return a.cost > b.cost; });
     else
         std::stable_sort(work.begin(), work.end(), [](const Work &a, const Work &b) {
+            if (a.phase != b.phase)
+                return a.phase < b.phase;
             if (a.it.kind != b.it.kind)
                 return a.it.kind < b.it.kind;
             return a.cost > b.cost;
         });
+    for (size_t i = 0; i < work.size(); ++i) {
+        if (i == 0 || work[i].phase != work[i - 1].phase)
+            p->launches.push_back(0);
+        ++p->launches.back();
+    }
     std::vector<BatchItem> items(work.size());
     for (size_t i = 0; i < work.size(); ++i)
         items[i] = work[i].it;
