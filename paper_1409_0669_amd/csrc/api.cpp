@@ -250,6 +250,9 @@ Cfg resolve_vector(int op, int t, int acc, int64_t n, std::initializer_list<cons
     return c;
 }
 
+// A launch holds fewer than 2^32 threads.
+bool too_many_threads(int64_t groups, int block) { return (double)groups * block >= 4294967296.0; }
+
 // The rows kernel's shape when the table names none, from the matrix's own
 // (GPU times of back-to-back calls on rotating matrices; "entry" is the size
 // class's fixed entry that the table held before).
@@ -272,6 +275,14 @@ Cfg resolve_vector(int op, int t, int acc, int64_t n, std::initializer_list<cons
 // iteration 87.7 us against 88.0), else 512 threads; the compensated forms as
 // few threads as take 8 packs each (16384 x 16384 bf16 83.8 us at 256 threads, 116
 // at 512; 20001 x 5000 f32 64.9 at 256, 86.8 at 512), and four long f64 or bf16 lines (f64 300 us at 16384 x 16384, 303 with two; bf16 90, 97).
+//
+// Tall matrices of that size, of lines up to 1500 packs (512 in the compensated forms): four
+// lines, eight from 2^20 lines of one wave on, and 256 threads (64): their
+// work-groups are short, so that starting them and summing their waves is what
+// counts: 2^22 x 100 f32 334 us (with 512 threads and two lines 4264), 2^18 x 1000
+// bf16 73 (294), 2^17 x 1500 f32 112 (174), 2^16 x 4000 f32 149 (167); compensated
+// 2^18 x 1000 bf16 97 (with 128 threads 184), 2^18 x 300 f64 123 (211).
+// Never more threads than a slice has packs, rounded up to a wave.
 // With the dot epilogue four lines always: fewer work-groups have its tail
 // (8192 x 8192 f64 80.5 us, 81.8 with two).  A line's sum does not depend on it.
 Cfg rows_rule(int t, int acc, int64_t L, int64_t K, bool with_dot)
@@ -283,7 +294,12 @@ Cfg rows_rule(int t, int acc, int64_t L, int64_t K, bool with_dot)
     c.rows = c.unroll = 2;
     c.split = 1;
     const int64_t packs = std::max<int64_t>(1, K / c.vec);
-    if (bytes >= 256 * mib) {
+    if (bytes >= 256 * mib && packs <= (comp ? 512 : 1500)) {
+        c.rows = 4;
+        c.block = comp ? 64 : 256;
+        if (comp && packs < 256)
+            c.unroll = 1;
+    } else if (bytes >= 256 * mib) {
         if (with_dot)
             c.rows = 4;
         const bool even = (double)packs / (double)(ceil_div(packs, 1024) * 1024) >= 0.9;
@@ -310,8 +326,17 @@ Cfg rows_rule(int t, int acc, int64_t L, int64_t K, bool with_dot)
         int64_t waves = groups < 3000 ? ceil_div(2048, groups) : packs < 1500 ? 2 : 4;
         waves = std::min<int64_t>({waves, ceil_div(packs, 64), 16});
         c.block = (int)(64 * waves);
-        if (packs <= c.block)
-            c.unroll = 1;
+    }
+    if (packs <= 64 && L > 1 << 20)
+        c.rows = 8;
+    c.block = (int)std::min<int64_t>(c.block, ceil_div(ceil_div(packs, c.split), 64) * 64);
+    if (packs <= c.block)
+        c.unroll = 1;
+    while (too_many_threads(ceil_div(L, c.rows) * c.split, c.block) && (c.rows < 8 || c.block > 64)) {
+        if (c.rows < 8)
+            c.rows *= 2;
+        else
+            c.block -= 64;
     }
     c.grid = (int)std::min<int64_t>(ceil_div(L, c.rows) * c.split, 0x7fffffff);
     return c;
@@ -343,7 +368,7 @@ Cfg resolve_rows(int t, int acc, int64_t L, int64_t K, const void *A, const void
         split = std::min<int64_t>(split, std::max<int64_t>(1, kpack / (2 * c.block)));
     }
     split = std::max<int64_t>(1, std::min<int64_t>(split, std::max<int64_t>(1, K)));
-    split = std::min<int64_t>(split, (int64_t)(0x7fffffff / std::max<int64_t>(1, groups)));
+    split = std::max<int64_t>(1, std::min<int64_t>(split, 0x7fffffff / std::max<int64_t>(1, groups)));
     c.split = (int)split;
     c.grid = (int)std::min<int64_t>(groups * split, 0x7fffffff); // reported only: work-groups launched
     // No more threads than the packs of a slice: a table entry tuned on long
@@ -456,7 +481,7 @@ Cfg resolve_cols(int t, int acc, int64_t L, int64_t K, const void *A, int64_t ld
         split = std::min<int64_t>(split, std::max<int64_t>(1, L / (waves * 16)));
     }
     split = std::max<int64_t>(1, std::min<int64_t>(split, std::max<int64_t>(1, L)));
-    split = std::min<int64_t>(split, (int64_t)(0x7fffffff / std::max<int64_t>(1, tiles)));
+    split = std::max<int64_t>(1, std::min<int64_t>(split, 0x7fffffff / std::max<int64_t>(1, tiles)));
     c.split = (int)split;
     c.grid = (int)std::min<int64_t>(tiles * split, 0x7fffffff); // reported only: work-groups launched
     return c;
@@ -1061,6 +1086,15 @@ static Cfg gemv_cfg(bwla_dtype t, int acc, const GemvPlan &g, const void *A, int
     return g.rows ? resolve_rows(t, acc, g.L, g.K, A, x, with_dot) : resolve_cols(t, acc, g.L, g.K, A, lda);
 }
 
+static bwla_status gemv_fits(const GemvPlan &g, const Cfg &c)
+{
+    const int64_t groups = (g.rows ? ceil_div(g.L, c.rows) : ceil_div(g.K, cols_tile(c))) * c.split;
+    if (too_many_threads(groups, c.block))
+        return fail(BWLA_ERR_UNSUPPORTED, "%lld work-groups of %d threads: a launch holds fewer than 2^32 threads",
+                    (long long)groups, c.block);
+    return BWLA_OK;
+}
+
 // Shared body of bwla_gemv and bwla_gemv_dot (w == NULL: no epilogue).
 static bwla_status gemv_common(bwla_dtype t, bwla_acc acc, bwla_layout layout, int trans, int64_t m,
                                int64_t n, const void *A, int64_t lda, const void *x, bwla_dtype out_t,
@@ -1123,6 +1157,8 @@ static bwla_status gemv_common(bwla_dtype t, bwla_acc acc, bwla_layout layout, i
     const bool comp = acc == BWLA_ACC_COMPENSATED;
     const int of64 = out_t == BWLA_F64, df64 = dot_t == BWLA_F64;
     Cfg c = gemv_cfg(t, acc, g, A, lda, x, fused);
+    if ((st = gemv_fits(g, c)) != BWLA_OK)
+        return st;
     size_t off = 0;
     const size_t need = gemv_ws(g, c, fused, &off);
     if (need && (!ws || ws_bytes < need))
@@ -1241,6 +1277,8 @@ bwla_status bwla_gemv_ex(bwla_dtype t, bwla_acc acc, bwla_layout layout, int tra
     size_t need = off_g;
     if (g.in_len > 0) {
         c = gemv_cfg(t, acc, g, A, lda, xs);
+        if ((st = gemv_fits(g, c)) != BWLA_OK)
+            return st;
         need += gemv_ws(g, c, false, nullptr);
     }
     if (!ws || ws_bytes < need)
