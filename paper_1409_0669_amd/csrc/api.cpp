@@ -253,14 +253,62 @@ Cfg resolve_vector(int op, int t, int acc, int64_t n, std::initializer_list<cons
 // A launch holds fewer than 2^32 threads.
 bool too_many_threads(int64_t groups, int block) { return (double)groups * block >= 4294967296.0; }
 
+// Few long lines, in as many slices as fill the chip.  A CU takes about 30 GB/s from
+// HBM (one line of 800 MB in one work-group: 31 GB/s), so the time is the bytes at the
+// chip's rate times how unevenly the work-groups fill the CUs, and a split adds its second
+// kernel (see cols_rule; about 1.4 us for 128 slices of one line).  From 256 MiB on the
+// cheapest split is taken, below that one that saves 10 %.  Two lines share the loads of x
+// from 16 MB on and four from 128 MB on, when x no longer stays in the caches (two for
+// compensated f32: L = 128 of 2 MB 48 us, with four 51).  f32, one slice per line -> this: 1 x 2e6
+// 264 us -> 10, 2 x 4e6 515 -> 14, 128 x 62500 14.6 -> 10.6, 4 x 5e7 9700 -> 150, 300 x 666666 176 ->
+// 129, 1000 x 200000 130 -> 117.
+// 512 lines and more of less than 256 MiB stay whole, with a work-group each where
+// that fills the CUs better (600 x 13333 10.8 -> 10.0).
+void few_lines(Cfg &c, int t, bool comp, int64_t L, int64_t K, int64_t packs)
+{
+    const double bytes = (double)L * K * dsize(t);
+    const int64_t cus = 256;
+    const bool large = bytes >= 268435456.0;
+    auto cost = [&](int64_t groups, int64_t split) {
+        const double n = (double)groups * (double)split;
+        const double us = bytes / 7.2e6 * ceil(n / cus) * cus / n;
+        return split > 1 ? us + 2.0 + 0.08 * (double)std::min<int64_t>(split, 8) + 0.012 * (double)split : us;
+    };
+    const int64_t groups = ceil_div(L, c.rows);
+    if (groups >= 4 * cus || L < 1)
+        return;
+    if (L >= 512 && !large) {
+        if (c.rows > 1 && cost(L, 1) < 0.9 * cost(groups, 1)) {
+            c.rows = 1;
+            c.block = (int)std::min<int64_t>(c.block, 64 * ceil_div(2048, L));
+        }
+        return;
+    }
+    int rows = bytes < 1.6e7 ? 1 : bytes < 1.28e8 || (comp && t == BWLA_F32) ? 2 : 4;
+    while (rows > 1 && rows > L + L / 3) // 3 lines take 4
+        rows /= 2;
+    const int64_t sliced = ceil_div(L, rows), most = std::max<int64_t>(1, packs / 128);
+    double best = large ? 1e300 : 0.9 * cost(groups, c.split);
+    for (int64_t fill = cus / 4; fill <= 4 * cus; fill *= 2) { // work-groups
+        const int64_t split = std::min(fill / sliced, most);
+        if (split > (large ? 0 : 1) && cost(sliced, split) < best) {
+            best = cost(sliced, split);
+            c.rows = rows;
+            c.split = (int)split;
+            c.block = rows == 4 ? 256 : 512;
+            c.unroll = 2;
+        }
+    }
+}
+
 // The rows kernel's shape when the table names none, from the matrix's own
 // (GPU times of back-to-back calls on rotating matrices; "entry" is the size
 // class's fixed entry that the table held before).
 //
-// One slice per line: a split's second kernel costs more than the work-groups
-// it adds give, even for few lines (500 x 500 f64 3.3 us against 5.5 with the
-// entry's split of 3, 500 x 30000 f32 12.1 against 17.6 with 5).  Only 16384 x 16384 f64
-// keeps two (295 us against 301).
+// One slice per line where the lines alone fill the CUs: a split's second kernel costs
+// more than its work-groups give (500 x 500 f64 3.3 us against 5.5 with the entry's split
+// of 3, 500 x 30000 f32 12.1 against 17.6 with 5; only 16384 x 16384 f64 keeps two, 295
+// us against 301).  few_lines has the rest.
 //
 // Below 256 MiB two lines and two packs of each per thread, and as few waves
 // per line as leave 8 on each CU: 4096 x 4096 with one wave per pair of lines takes
@@ -283,7 +331,7 @@ bool too_many_threads(int64_t groups, int block) { return (double)groups * block
 // bf16 73 (294), 2^17 x 1500 f32 112 (174), 2^16 x 4000 f32 149 (167); compensated
 // 2^18 x 1000 bf16 97 (with 128 threads 184), 2^18 x 300 f64 123 (211).
 // Never more threads than a slice has packs, rounded up to a wave.
-// With the dot epilogue four lines always: fewer work-groups have its tail
+// With the dot epilogue four lines from 2048 on: fewer work-groups have its tail
 // (8192 x 8192 f64 80.5 us, 81.8 with two).  A line's sum does not depend on it.
 Cfg rows_rule(int t, int acc, int64_t L, int64_t K, bool with_dot)
 {
@@ -300,8 +348,6 @@ Cfg rows_rule(int t, int acc, int64_t L, int64_t K, bool with_dot)
         if (comp && packs < 256)
             c.unroll = 1;
     } else if (bytes >= 256 * mib) {
-        if (with_dot)
-            c.rows = 4;
         const bool even = (double)packs / (double)(ceil_div(packs, 1024) * 1024) >= 0.9;
         c.block = 512;
         if (comp) {
@@ -329,6 +375,9 @@ Cfg rows_rule(int t, int acc, int64_t L, int64_t K, bool with_dot)
     }
     if (packs <= 64 && L > 1 << 20)
         c.rows = 8;
+    few_lines(c, t, comp, L, K, packs);
+    if (with_dot && bytes >= 256 * mib && L >= 2048)
+        c.rows = std::max(c.rows, 4);
     c.block = (int)std::min<int64_t>(c.block, ceil_div(ceil_div(packs, c.split), 64) * 64);
     if (packs <= c.block)
         c.unroll = 1;
