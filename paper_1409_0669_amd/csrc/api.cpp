@@ -496,6 +496,8 @@ Cfg cols_rule(int t, int acc, int64_t L, int64_t K, bool line_aligned)
         c.unroll = deep ? 8 : 4;
         c.block = deep ? 256 : 512;
     }
+    while (c.block > 64 && too_many_threads(ceil_div(K, cols_tile(c)) * c.split, c.block))
+        c.block = c.block / 128 * 64;
     c.grid = (int)std::min<int64_t>(ceil_div(K, cols_tile(c)) * c.split, 0x7fffffff);
     return c;
 }
