@@ -498,6 +498,10 @@ Cfg cols_rule(int t, int acc, int64_t L, int64_t K, bool line_aligned)
     }
     while (c.block > 64 && too_many_threads(ceil_div(K, cols_tile(c)) * c.split, c.block))
         c.block = c.block / 128 * 64;
+    if (too_many_threads(ceil_div(K, cols_tile(c)) * c.split, c.block)) {
+        c.rows = 1; // the widest tile
+        c.vec = native_vec(t);
+    }
     c.grid = (int)std::min<int64_t>(ceil_div(K, cols_tile(c)) * c.split, 0x7fffffff);
     return c;
 }
