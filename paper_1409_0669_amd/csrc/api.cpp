@@ -451,16 +451,47 @@ Cfg resolve_rows(int t, int acc, int64_t L, int64_t K, const void *A, const void
 // One line per access (k_gemv_cols) stays where it is the faster: plain f64
 // from 64 MiB and f32 from 1 GiB with lines on cache lines, 8 bytes per lane
 // (f64 16384 x 16384 298 us against 308, f32 151 against 155).
-Cfg cols_rule(int t, int acc, int64_t L, int64_t K, bool line_aligned)
+//
+// The ends of the range, where most of a tile or of a work-group has no data (GPU times
+// of 60 MB with the choice above -> this one):
+//  - Lines shorter than a pack, or elements off their alignment: one element per lane
+//    (two for bf16), 16 lines in flight (f32 5e6 x 3 1292 us -> 110, bf16 4.3e6 x 7 1847 -> 117).
+//  - Lines that leave a quarter of their tile empty: the narrowest tile that holds
+//    them, one slice per CU (f64 3.75e6 x 2 176 -> 40, bf16 9e5 x 33 60 -> 27).
+Cfg cols_rule(int t, int acc, int64_t L, int64_t K, int vec, bool line_aligned)
 {
     const bool comp = acc == BWLA_ACC_COMPENSATED, f64 = t == BWLA_F64;
+    const int native = native_vec(t);
     const double bytes = (double)L * K * dsize(t);
     Cfg c{};
     auto tiles_of = [&](int lines) {
         c.rows = lines;
         return ceil_div(K, cols_tile(c));
     };
-    if (!comp && line_aligned && t != BWLA_BF16 && bytes >= (f64 ? 64.0 : 1024.0) * (1 << 20)) {
+    auto one_line = [&](int v, int block, int unroll, int64_t split) {
+        c.vec = v;
+        c.rows = 1;
+        c.block = block;
+        c.unroll = unroll;
+        c.split = (int)split;
+    };
+    int narrow = 8; // lines per access of the narrowest tile that holds a line
+    c.vec = native;
+    while (narrow > 1 && tiles_of(narrow) > 1)
+        narrow /= 2;
+    if (vec < native || K < native) {
+        const int v = std::min(vec, t == BWLA_BF16 && K > 1 ? 2 : 1);
+        const int64_t fill = (bytes < 32.0 * (1 << 20) ? 256 : 1024) / std::max<int64_t>(1, ceil_div(K, 64 * v));
+        one_line(v, comp && f64 ? 1024 : 512, 16, std::max<int64_t>(1, std::min<int64_t>(fill, L / 128)));
+    } else if (narrow > 1 && (narrow == 8 || 4 * K <= 3 * (64 / narrow) * native)) {
+        const int64_t split = std::max<int64_t>(1, std::min<int64_t>(bytes < 8e6 ? 128 : 256, L / 64));
+        c.rows = narrow;
+        c.block = 512;
+        c.unroll = f64 || (t == BWLA_F32 && !comp) ? 4 : 8;
+        // a single slice, at a CU's rate, or the second kernel
+        c.split = bytes / 7.2e6 * 256.0 < bytes / 7.2e6 * 256.0 / (double)split + 2.5 ? 1 : (int)split;
+    } else if (!comp && line_aligned && t != BWLA_BF16 && bytes >= (f64 ? 64.0 : 1024.0) * (1 << 20) &&
+               K >= 128 * (int64_t)(8 / dsize(t))) {
         const bool large = f64 && bytes >= 1073741824.0;
         c.vec = (int)(8 / dsize(t));
         c.unroll = 4;
@@ -498,7 +529,7 @@ Cfg cols_rule(int t, int acc, int64_t L, int64_t K, bool line_aligned)
     }
     while (c.block > 64 && too_many_threads(ceil_div(K, cols_tile(c)) * c.split, c.block))
         c.block = c.block / 128 * 64;
-    if (too_many_threads(ceil_div(K, cols_tile(c)) * c.split, c.block)) {
+    if (vec == native && too_many_threads(ceil_div(K, cols_tile(c)) * c.split, c.block)) {
         c.rows = 1; // the widest tile
         c.vec = native_vec(t);
     }
@@ -512,8 +543,8 @@ Cfg resolve_cols(int t, int acc, int64_t L, int64_t K, const void *A, int64_t ld
     Cfg c;
     c.vec = fit_vec(u.vec ? u.vec : native_vec(t), dsize(t), {A});
     const bool grouped = c.vec == native_vec(t) && K >= c.vec;
-    if (grouped && !u.block && !u.unroll && !u.grid && !u.rows && !u.split)
-        return cols_rule(t, acc, L, K, (uintptr_t)A % 128 == 0 && ld * (int64_t)dsize(t) % 128 == 0);
+    if (!u.block && !u.unroll && !u.grid && !u.rows && !u.split && (!u.vec || u.vec == native_vec(t)))
+        return cols_rule(t, acc, L, K, c.vec, (uintptr_t)A % 128 == 0 && ld * (int64_t)dsize(t) % 128 == 0);
     c.block = u.block ? u.block : 512;
     c.unroll = u.unroll ? u.unroll : 4; // lines in flight per wave: 1 to 32
     while (c.unroll > 8 && (size_t)c.unroll * c.vec * dsize(t) > kColsLoadBytes)
