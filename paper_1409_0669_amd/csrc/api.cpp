@@ -458,6 +458,9 @@ Cfg resolve_rows(int t, int acc, int64_t L, int64_t K, const void *A, const void
 //    (two for bf16), 16 lines in flight (f32 5e6 x 3 1292 us -> 110, bf16 4.3e6 x 7 1847 -> 117).
 //  - Lines that leave a quarter of their tile empty: the narrowest tile that holds
 //    them, one slice per CU (f64 3.75e6 x 2 176 -> 40, bf16 9e5 x 33 60 -> 27).
+//  - Fewer than 40 lines, up to 128 of long ones: one line per access and one wave per
+//    work-group (of small matrices one for four lines), f32 1 x 1.5e7 210 -> 35, compensated 8 x
+//    1.9e6 52 -> 16, 16 x 9.4e5 30 -> 14; f64 100 x 500000 107 -> 62.
 Cfg cols_rule(int t, int acc, int64_t L, int64_t K, int vec, bool line_aligned)
 {
     const bool comp = acc == BWLA_ACC_COMPENSATED, f64 = t == BWLA_F64;
@@ -479,10 +482,17 @@ Cfg cols_rule(int t, int acc, int64_t L, int64_t K, int vec, bool line_aligned)
     c.vec = native;
     while (narrow > 1 && tiles_of(narrow) > 1)
         narrow /= 2;
+    const int pack = std::min(native, 4);
     if (vec < native || K < native) {
         const int v = std::min(vec, t == BWLA_BF16 && K > 1 ? 2 : 1);
         const int64_t fill = (bytes < 32.0 * (1 << 20) ? 256 : 1024) / std::max<int64_t>(1, ceil_div(K, 64 * v));
         one_line(v, comp && f64 ? 1024 : 512, 16, std::max<int64_t>(1, std::min<int64_t>(fill, L / 128)));
+    } else if (L < 40 || (L <= 128 && K >= 196608 * (int64_t)pack)) {
+        const bool small = bytes < 32.0 * (1 << 20);
+        int v = pack;
+        while (small && v > 1 && K < 512 * 64 * (int64_t)v)
+            v /= 2;
+        one_line(v, small ? (int)(64 * std::max<int64_t>(1, std::min<int64_t>(8, ceil_div(L, 4)))) : 64, small && L >= 4 ? 4 : 2, 1);
     } else if (narrow > 1 && (narrow == 8 || 4 * K <= 3 * (64 / narrow) * native)) {
         const int64_t split = std::max<int64_t>(1, std::min<int64_t>(bytes < 8e6 ? 128 : 256, L / 64));
         c.rows = narrow;
@@ -490,7 +500,7 @@ Cfg cols_rule(int t, int acc, int64_t L, int64_t K, int vec, bool line_aligned)
         c.unroll = f64 || (t == BWLA_F32 && !comp) ? 4 : 8;
         // a single slice, at a CU's rate, or the second kernel
         c.split = bytes / 7.2e6 * 256.0 < bytes / 7.2e6 * 256.0 / (double)split + 2.5 ? 1 : (int)split;
-    } else if (!comp && line_aligned && t != BWLA_BF16 && bytes >= (f64 ? 64.0 : 1024.0) * (1 << 20) &&
+    } else if (!comp && line_aligned && t != BWLA_BF16 && bytes >= (f64 ? 64.0 : 1024.0) * (1 << 20) && L >= 512 &&
                K >= 128 * (int64_t)(8 / dsize(t))) {
         const bool large = f64 && bytes >= 1073741824.0;
         c.vec = (int)(8 / dsize(t));

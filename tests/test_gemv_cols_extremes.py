@@ -1,5 +1,6 @@
 """The cols GEMV at the ends of its range: lines shorter than a pack or than a
-tile, and widths near the thread count that one launch holds."""
+tile, a handful of very long lines, and widths near the thread count that one
+launch holds."""
 from __future__ import annotations
 
 import ctypes
@@ -58,7 +59,8 @@ def test_short_lines_keep_loads_in_flight_and_the_chip_full():
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", ["f64", "f32", "bf16"])
 @pytest.mark.parametrize("lines,k", [(300_001, 1), (70_001, 2), (40_003, 3), (900_000, 5), (90_001, 7), (50_000, 9),
-                                     (33_333, 17), (20_001, 33)])
+                                     (33_333, 17), (20_001, 33), (1, 1_000_003), (2, 500_001), (3, 4_000_003),
+                                     (8, 70_001), (33, 9_999), (39, 1_100_000), (100, 300_001), (500, 200_000)])
 def test_extremes_are_exact(dtype, lines, k):
     need_gpu()
     from paper_1409_0669_amd import ops
