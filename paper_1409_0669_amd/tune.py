@@ -355,9 +355,8 @@ GEMV_GROUPS_PER_CU = (0, 1, 2, 4, 8, 16, 32, 64)
 def _rows_candidates(dtype, quick, cus=256):
     native = 16 // torch.tensor([], dtype=dtype).element_size()
     vecs = (native,) if quick else (max(1, native // 2), native)
-    return [_gemv_rule(native)] + [dict(block=b, vec=v, rows=r, unroll=u, split=0, grid=g * cus)
-                                   for b in (64, 128, 256, 512, 1024) for v in vecs for r in (1, 2, 4, 8)
-                                   for u in (1, 2) for g in GEMV_GROUPS_PER_CU]
+    return [dict(block=b, vec=v, rows=r, unroll=u, split=0, grid=g * cus) for b in (64, 128, 256, 512, 1024)
+            for v in vecs for r in (1, 2, 4, 8) for u in (1, 2) for g in GEMV_GROUPS_PER_CU]
 
 
 def _gemv_rule(native):
@@ -367,6 +366,23 @@ def _gemv_rule(native):
 
 
 FIXED_GAIN = 0.93  # the rule's rate against a fixed entry's from which the rule stays
+
+
+def rule_or_fixed(rule, rule_rates, fixed, fixed_score, fixed_rates):
+    """The entry of a size class and its report: the library's rule, unless the
+    best fixed entry is clearly better over the shapes tuned on (the rule follows
+    shapes that were not, and saves launches that GPU times do not see).  The
+    report has both sides, whichever is kept."""
+    rule_score = statistics.geometric_mean(rule_rates)
+    kept = rule_score >= FIXED_GAIN * fixed_score
+    fixed_rates = [fixed_rates[i] for i in range(len(rule_rates))]
+    return rule if kept else fixed, {
+        "best": rule if kept else fixed,
+        "best_gbs_per_shape": [round(r, 1) for r in (rule_rates if kept else fixed_rates)],
+        "best_gbs_geomean": round(rule_score if kept else fixed_score, 1),
+        "default_gbs_per_shape": [round(r, 1) for r in rule_rates],
+        "fixed": fixed, "fixed_gbs_per_shape": [round(r, 1) for r in fixed_rates],
+        "fixed_gbs_geomean": round(fixed_score, 1)}
 
 
 def _cols_candidates(dtype, quick, cus=256):
@@ -382,7 +398,7 @@ def _cols_candidates(dtype, quick, cus=256):
     # A per lane in flight)
     single = [dict(block=b, vec=v, unroll=u, split=0, grid=g * cus, rows=1) for b in (512, 1024) for v in vecs
               for u in (4, 8, 16) if u <= 8 or u * v * es <= 128 for g in GEMV_GROUPS_PER_CU]
-    return [_gemv_rule(native)] + grouped + single
+    return grouped + single
 
 
 # GEMV shapes tuned; each size class is tuned on every shape that falls in it
@@ -443,9 +459,9 @@ def _ger_candidates(dtype, quick):
 
 def _batch_candidates(quick):
     # the work-group size and the packs of a GEMV row each lane of a
-    # tile owns (fewer packs: more lanes share a row)
+    # tile owns (fewer packs: more lanes share a row; more than 8 act as 8)
     return [dict(block=b, unroll=u) for b in ((256, 512) if quick else (128, 256, 512))
-            for u in ((8, 16) if quick else (4, 8, 16, 32))]
+            for u in ((4, 8) if quick else (1, 2, 4, 8))]
 
 
 # the uneven batch tuned on: 512 GEMVs with M, N log-uniform in [32, 4096] and
@@ -545,21 +561,16 @@ def _tune_all(dtypes, quick, log, ops_, vec_sizes, gemv_shapes, ger_shapes, max_
             for acc in accs:
                 for cls, shapes in sorted(by_class.items()):
                     ws = [Workload("gemv", dt, n=n, m=m, layout=layout, acc=acc) for (m, n) in shapes]
-                    default = [w.bytes / (time_ms(w.run, reps=10) * 1e-3) / 1e9 for w in ws]
                     cfg, score, rates = multi_shape_pick(ws, cands_g, refine=refine)
-                    if statistics.geometric_mean(default) >= FIXED_GAIN * score:
-                        # the library's rule (the default here) stays unless one fixed entry is
-                        # clearly better: it follows shapes that were not tuned on, and
-                        # saves launches that this GPU-time measure does not see
-                        cfg, rates = _gemv_rule(ws[0].native), dict(enumerate(default))
-                        score = statistics.geometric_mean(default)
+                    # (an empty entry is in force again: the rule, timed as the leaders were)
+                    default = [w.bytes / (statistics.median(time_ms(w.run, reps=6) for _ in range(5)) * 1e-3) / 1e9
+                               for w in ws]
+                    cfg, rec = rule_or_fixed(_gemv_rule(ws[0].native), default, cfg, score, rates)
                     entries.append((ws[0].table_op, dt, acc, cls, cfg))
-                    rec = {"op": "gemv_" + layout, "dtype": dn, "acc": acc, "class": cls, "shapes": shapes,
-                           "best": cfg, "best_gbs_per_shape": [round(rates[i], 1) for i in range(len(ws))],
-                           "best_gbs_geomean": round(score, 1), "default_gbs_per_shape": [round(d, 1) for d in default]}
+                    rec = {"op": "gemv_" + layout, "dtype": dn, "acc": acc, "class": cls, "shapes": shapes, **rec}
                     report["results"].append(rec)
-                    log("gemv_%-4s %-4s %-11s class %d %-40s best %s GB/s default %s GB/s %s" % (
-                        layout, dn, acc, cls, " ".join("%dx%d" % sh for sh in shapes), rec["best_gbs_per_shape"],
+                    log("gemv_%-4s %-4s %-11s class %d %-40s fixed %s GB/s rule %s GB/s, entry %s" % (
+                        layout, dn, acc, cls, " ".join("%dx%d" % sh for sh in shapes), rec["fixed_gbs_per_shape"],
                         rec["default_gbs_per_shape"], cfg))
                     del ws
         for (m, n) in (ger_shapes if "ger" in ops_ else ()):
