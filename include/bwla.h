@@ -120,7 +120,7 @@ typedef enum BWLA_ENUM_INT {
  *         to 8; GEMV_COLS takes 16 and 32 while those lines hold at most 128
  *         bytes of A per thread, and halves larger values until they do)
  * DOT, NRM2 and CG over at most 256 KiB (all vectors together) run as one
- * work-group, in one launch, whatever the table says.
+ * work-group, in one launch, where their entry is empty.
  * GEMV_ROWS work-groups are never larger than the packs of one slice of a
  * line (rounded up to 64 threads), whatever the table says.
  * grid:   number of work-groups (streaming and reductions).  For GEMV_ROWS

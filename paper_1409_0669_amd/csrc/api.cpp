@@ -198,13 +198,15 @@ int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // better and keep the second stage small).
 constexpr int kOpCg = BWLA_OP_CG;
 
-// Bytes up to which a reduction runs as one work-group, whatever its table entry
-// says: one launch instead of two.  There the single work-group's time on
+// Reductions of less than 1 MiB without a table entry.  Up to 256 KiB one work-group:
+// one launch instead of two.  There the single work-group's time on
 // the GPU meets that of the two kernels (f64 dot: 16 KB 2.4 us against 3.9 at
-// best with more work-groups and 4.2 with the table's entries, 128 KB 3.2
+// best with more work-groups, 128 KB 3.2
 // against 4.0, 256 KB 4.0 against 4.1, 640 KB 6.7 against 4.2), while the host
-// saves a launch, 11.2 -> 7.8 us per call from Python.
-constexpr double kOneGroupBytes = 262144;
+// saves a launch, 11.2 -> 7.8 us per call from Python.  Above, one pack per thread in
+// work-groups of 256 (280 to 900 KB, 18 types, operations and modes: 4.0 to 5.9 us, with
+// four packs 4.2 to 6.5; the best fixed entry of each 4.0 to 5.9).  An entry is followed as it is.
+constexpr double kOneGroupBytes = 262144, kSmallBytes = 1048576;
 
 Cfg resolve_vector(int op, int t, int acc, int64_t n, std::initializer_list<const void *> ptrs, int nstreams)
 {
@@ -212,7 +214,10 @@ Cfg resolve_vector(int op, int t, int acc, int64_t n, std::initializer_list<cons
     const double bytes = (double)n * dsize(t) * nstreams;
     bwla_config u = lookup(op, t, reduction ? acc : BWLA_ACC_PLAIN, bytes);
     Cfg c;
-    if (reduction && bytes <= kOneGroupBytes) { // two packs in flight per thread
+    const bool small = reduction && bytes < kSmallBytes && !u.block && !u.vec && !u.unroll && !u.grid && !u.increment;
+    if (small)
+        u.unroll = 1;
+    if (small && bytes <= kOneGroupBytes) { // two packs in flight per thread
         c.vec = fit_vec(native_vec(t), dsize(t), ptrs);
         c.unroll = 2;
         c.block = (int)std::min<int64_t>(1024, std::max<int64_t>(1, ceil_div(n / c.vec, 128)) * 64);

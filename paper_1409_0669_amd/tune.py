@@ -368,13 +368,13 @@ def _gemv_rule(native):
 FIXED_GAIN = 0.93  # the rule's rate against a fixed entry's from which the rule stays
 
 
-def rule_or_fixed(rule, rule_rates, fixed, fixed_score, fixed_rates):
+def rule_or_fixed(rule, rule_rates, fixed, fixed_score, fixed_rates, gain=FIXED_GAIN):
     """The entry of a size class and its report: the library's rule, unless the
     best fixed entry is clearly better over the shapes tuned on (the rule follows
     shapes that were not, and saves launches that GPU times do not see).  The
     report has both sides, whichever is kept."""
     rule_score = statistics.geometric_mean(rule_rates)
-    kept = rule_score >= FIXED_GAIN * fixed_score
+    kept = rule_score >= gain * fixed_score
     fixed_rates = [fixed_rates[i] for i in range(len(rule_rates))]
     return rule if kept else fixed, {
         "best": rule if kept else fixed,
@@ -542,6 +542,16 @@ def _tune_all(dtypes, quick, log, ops_, vec_sizes, gemv_shapes, ger_shapes, max_
                         ws.append(w)
                         sweeps.append(res)
                     cfg, score, rates = pick_from_sweeps(ws, sweeps, refine=refine)
+                    if op in REDUCING and cls == 0:
+                        # the library's rule for small reductions stays: a fixed entry would also take the
+                        # sizes of one work-group, which are not among these
+                        rule = [w.bytes / (statistics.median(time_ms(w.run, reps=6) for _ in range(5)) * 1e-3) / 1e9
+                                for w in ws]
+                        cfg, both = rule_or_fixed(dict(block=0, vec=0, unroll=0, increment=0, grid=0), rule, cfg, score,
+                                                  rates, gain=0.0)
+                        rates = both["best_gbs_per_shape"]
+                        for i, rec in enumerate(recs):
+                            rec["fixed_entry"], rec["fixed_entry_gbs"] = both["fixed"], both["fixed_gbs_per_shape"][i]
                     for i, rec in enumerate(recs):
                         rec["class_entry"], rec["class_entry_gbs"] = cfg, round(rates[i], 1)
                     log("%-9s %-4s %-11s class %d entry over n=%s: %s, %s GB/s" % (
