@@ -492,7 +492,7 @@ Cfg cols_rule(int t, int acc, int64_t L, int64_t K, int vec, bool line_aligned)
         const int v = std::min(vec, t == BWLA_BF16 && K > 1 ? 2 : 1);
         const int64_t fill = (bytes < 32.0 * (1 << 20) ? 256 : 1024) / std::max<int64_t>(1, ceil_div(K, 64 * v));
         one_line(v, comp && f64 ? 1024 : 512, 16, std::max<int64_t>(1, std::min<int64_t>(fill, L / 128)));
-    } else if (L < 40 || (L <= 128 && K >= 196608 * (int64_t)pack)) {
+    } else if (L < 40 || (L <= 128 && bytes >= 256.0 * (1 << 20))) {
         const bool small = bytes < 32.0 * (1 << 20);
         int v = pack;
         while (small && v > 1 && K < 512 * 64 * (int64_t)v)
