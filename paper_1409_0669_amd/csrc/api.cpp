@@ -329,12 +329,14 @@ void few_lines(Cfg &c, int t, bool comp, int64_t L, int64_t K, int64_t packs)
 // few threads as take 8 packs each (16384 x 16384 bf16 83.8 us at 256 threads, 116
 // at 512; 20001 x 5000 f32 64.9 at 256, 86.8 at 512), and four long f64 or bf16 lines (f64 300 us at 16384 x 16384, 303 with two; bf16 90, 97).
 //
-// Tall matrices of that size, of lines up to 1500 packs (512 in the compensated forms): four
-// lines, eight from 2^20 lines of one wave on, and 256 threads (64): their
-// work-groups are short, so that starting them and summing their waves is what
+// Tall matrices of that size, of lines up to 1500 packs (400 in the compensated forms): 256
+// threads (64) and two lines, four up to 192 packs (256), eight from 2^20 lines of one wave
+// on: their work-groups are short, so that starting them and summing their waves is what
 // counts: 2^22 x 100 f32 334 us (with 512 threads and two lines 4264), 2^18 x 1000
 // bf16 73 (294), 2^17 x 1500 f32 112 (174), 2^16 x 4000 f32 149 (167); compensated
-// 2^18 x 1000 bf16 97 (with 128 threads 184), 2^18 x 300 f64 123 (211).
+// 2^18 x 1000 bf16 97 (with 128 threads 184), 2^18 x 300 f64 123 (211).  More lines lose where
+// their distance is a power of two (16384 x 2048 f64: 512 threads and two lines 43.5, 256
+// and four 48.1).
 // Never more threads than a slice has packs, rounded up to a wave.
 // With the dot epilogue four lines from 2048 on: fewer work-groups have its tail
 // (8192 x 8192 f64 80.5 us, 81.8 with two).  A line's sum does not depend on it.
@@ -347,9 +349,9 @@ Cfg rows_rule(int t, int acc, int64_t L, int64_t K, bool with_dot)
     c.rows = c.unroll = 2;
     c.split = 1;
     const int64_t packs = std::max<int64_t>(1, K / c.vec);
-    if (bytes >= 256 * mib && packs <= (comp ? 512 : 1500)) {
-        c.rows = 4;
-        c.block = comp ? 64 : 256;
+    if (bytes >= 256 * mib && packs <= (comp ? 400 : 1500)) {
+        c.rows = packs <= (comp ? 256 : 192) ? 4 : 2;
+        c.block = comp ? 64 : packs == 1024 ? 512 : 256;
         if (comp && packs < 256)
             c.unroll = 1;
     } else if (bytes >= 256 * mib) {
