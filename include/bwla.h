@@ -67,8 +67,9 @@ typedef enum BWLA_ENUM_INT {
 typedef enum BWLA_ENUM_INT { BWLA_F64 = 0, BWLA_F32 = 1, BWLA_BF16 = 2 } bwla_dtype;
 typedef enum BWLA_ENUM_INT { BWLA_ROW_MAJOR = 0, BWLA_COL_MAJOR = 1 } bwla_layout;
 
-/* Accumulation of reductions.  PLAIN: one running sum per thread in the
- * compute precision.  COMPENSATED: the running sum carries its rounding error
+/* Accumulation of reductions.  PLAIN: running sums in the compute precision,
+ * short ones where a thread has many terms: those of float32 and bf16 are then
+ * added up in float64.  COMPENSATED: the running sum carries its rounding error
  * (TwoSum) and, for f64/f32, the product error (TwoProduct by fma) -- the
  * Dot2 scheme of Ogita, Rump and Oishi; for bf16 the products are exact and
  * summed in float64 (less error than a float32 sum carrying its own, and

@@ -241,7 +241,9 @@ __device__ __forceinline__ void gemv_tile_rows(const BatchGemv &g, int64_t rb, i
             const int64_t r = base + j * RPW + sub;
             row[j] = A + (r < re ? r : re - 1) * g.lda;
         }
-        acc_t<T, COMP> acc[R];
+        // (a lane has at most 8 packs of rows that share a wave: one running sum)
+        std::conditional_t<!COMP && G < 64, Acc<compute_t<T>, false>, acc_t<T, COMP>> acc[R];
+        int taken = 0; // trips: packs of a row by this lane
         for (int64_t k = gl * V; k < whole; k += G * V) {
             Pack<T, V> a[R];
             const Pack<T, V> xv = load_pack<T, V>(x + k);
@@ -254,6 +256,10 @@ __device__ __forceinline__ void gemv_tile_rows(const BatchGemv &g, int64_t rb, i
 #pragma unroll
                 for (int j = 0; j < R; ++j)
                     acc[j].template add_prod<EXACT>(widen(a[j].v[e]), widen(xv.v[e]));
+            if (++taken % kRunPacks<T> == 0)
+#pragma unroll
+                for (int j = 0; j < R; ++j)
+                    acc[j].fold();
         }
         if (whole < n) {
             Pack<T, V> a[R];

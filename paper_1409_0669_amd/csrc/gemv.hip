@@ -107,8 +107,19 @@ __global__ __launch_bounds__(1024) void k_gemv_rows(int64_t L, int64_t K, const 
 
     // U trips of the pack loop per iteration, all loads first: R * U packs of
     // A in flight per thread.  Each row's sum still takes the packs in the
-    // order p, p + blockDim, ..., so U does not change any result.
+    // order p, p + blockDim, ..., and ends its runs at the same packs, so U does
+    // not change any result.
     acc_t<T, COMP> acc[R];
+    int taken = 0; // packs of a row by this thread
+    auto fold_rows = [&](int n) {
+        if constexpr (!COMP && kRunPacks<T> > 1) {
+            taken += n;
+            if (taken % kRunPacks<T> == 0)
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+                    acc[r].fold();
+        }
+    };
     int64_t p = pb + threadIdx.x;
     for (; p + (int64_t)(U - 1) * blockDim.x < pe; p += (int64_t)U * blockDim.x) {
         Pack<T, V> xv[U], av[U][R];
@@ -123,10 +134,14 @@ __global__ __launch_bounds__(1024) void k_gemv_rows(int64_t L, int64_t K, const 
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
-            for (int r = 0; r < R; ++r)
+            for (int r = 0; r < R; ++r) {
 #pragma unroll
                 for (int e = 0; e < V; ++e)
                     acc[r].template add_prod<EXACT>(widen(av[u][r].v[e]), widen(xv[u].v[e]));
+                if (kRunPacks<T> == 1)
+                    acc[r].fold();
+            }
+        fold_rows(U);
     }
     for (; p < pe; p += blockDim.x) {
         Pack<T, V> xv = load_pack<T, V>(v + p * V);
@@ -135,10 +150,14 @@ __global__ __launch_bounds__(1024) void k_gemv_rows(int64_t L, int64_t K, const 
         for (int r = 0; r < R; ++r)
             av[r] = load_pack_nt<T, V>(row[r] + p * V);
 #pragma unroll
-        for (int r = 0; r < R; ++r)
+        for (int r = 0; r < R; ++r) {
 #pragma unroll
             for (int e = 0; e < V; ++e)
                 acc[r].template add_prod<EXACT>(widen(av[r].v[e]), widen(xv.v[e]));
+            if (kRunPacks<T> == 1)
+                acc[r].fold();
+        }
+        fold_rows(1);
     }
     const int64_t tail = K - kpack * V; // < V elements, taken by the last slice
     if (s == split - 1 && threadIdx.x < tail) {
@@ -207,7 +226,17 @@ __global__ __launch_bounds__(1024) void k_gemv_cols(int64_t L, int64_t K, const 
 
     // LDS for the cross-wave combine (the hand-over path).
     __shared__ __attribute__((aligned(16))) DD red[TK];
-    acc_t<T, COMP> acc[V];
+    line_acc_t<T, COMP> acc[V];
+    int taken = 0; // lines by this wave
+    auto fold_cols = [&](int n) { // (runs of lines end where they do for every U and V)
+        if constexpr (!COMP && std::is_same_v<T, double>) {
+            taken += n;
+            if (taken % kRunLines == 0)
+#pragma unroll
+                for (int e = 0; e < V; ++e)
+                    acc[e].fold();
+        }
+    };
 
     // v[l] is read with the U lines' loads (no staging pass and no barrier
     // before the first loads of A).
@@ -226,10 +255,16 @@ __global__ __launch_bounds__(1024) void k_gemv_cols(int64_t L, int64_t K, const 
             }
             end_of_loads();
 #pragma unroll
-            for (int u = 0; u < U; ++u)
+            for (int u = 0; u < U; ++u) {
 #pragma unroll
                 for (int e = 0; e < V; ++e)
                     acc[e].template add_prod<EXACT>(widen(a[u].v[e]), widen(xv[u]));
+                if (U > kRunLines && u % kRunLines == kRunLines - 1 && u < U - 1)
+#pragma unroll
+                    for (int e = 0; e < V; ++e)
+                        acc[e].fold();
+            }
+            fold_cols(U);
         }
         for (; j < tn; j += nw) {
             Pack<T, V> a = load_pack_nt<T, V>(base + j * ld);
@@ -237,6 +272,7 @@ __global__ __launch_bounds__(1024) void k_gemv_cols(int64_t L, int64_t K, const 
 #pragma unroll
             for (int e = 0; e < V; ++e)
                 acc[e].template add_prod<EXACT>(widen(a.v[e]), xl);
+            fold_cols(1);
         }
     } else if (k0 < K) { // lines shorter than a pack
         for (; j < tn; j += nw) {
@@ -245,6 +281,7 @@ __global__ __launch_bounds__(1024) void k_gemv_cols(int64_t L, int64_t K, const 
             for (int e = 0; e < V; ++e)
                 if (kb + e >= 0)
                     acc[e].template add_prod<EXACT>(widen(base[j * ld + e]), xl);
+            fold_cols(1);
         }
     }
 
@@ -384,8 +421,11 @@ __global__ __launch_bounds__(1024) void k_gemv_cols_grouped(int64_t L, int64_t K
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
-            for (int e = 0; e < V; ++e)
+            for (int e = 0; e < V; ++e) {
                 acc[e].template add_prod<EXACT>(widen(a[u].v[e]), widen(xv.v[u]));
+                if (u % kRunLines == kRunLines - 1)
+                    acc[e].fold();
+            }
     }
     if (j < tn) { // the last trip: lines past the end re-read the last one and are not added
         Pack<T, V> a[U];
@@ -401,8 +441,11 @@ __global__ __launch_bounds__(1024) void k_gemv_cols_grouped(int64_t L, int64_t K
         for (int u = 0; u < U; ++u)
             if (j + u < tn)
 #pragma unroll
-                for (int e = 0; e < V; ++e)
+                for (int e = 0; e < V; ++e) {
                     acc[e].template add_prod<EXACT>(widen(a[u].v[e]), widen(xv[u]));
+                    if (u % kRunLines == kRunLines - 1)
+                        acc[e].fold();
+                }
     }
 
     // This thread's prior output, in flight during the sums below.

@@ -62,11 +62,14 @@ __global__ __launch_bounds__(1024) void k_dot(int64_t n, const T *x, const T *y,
         }
         end_of_loads();
 #pragma unroll
-        for (int u = 0; u < U; ++u)
+        for (int u = 0; u < U; ++u) {
 #pragma unroll
             for (int e = 0; e < V; ++e)
                 reduce_term<MODE, EXACT>(acc[u], widen(vx[u].v[e]),
                                          MODE == kRedDot ? widen(vy[u].v[e]) : C(0));
+            if (U <= 2)
+                acc[u].fold();
+        }
     }
     for (; p < end; p += stride) {
         Pack<T, V> vx = load_pack_nt<T, V>(x + p * V), vy;
@@ -75,6 +78,7 @@ __global__ __launch_bounds__(1024) void k_dot(int64_t n, const T *x, const T *y,
 #pragma unroll
         for (int e = 0; e < V; ++e)
             reduce_term<MODE, EXACT>(acc[0], widen(vx.v[e]), MODE == kRedDot ? widen(vy.v[e]) : C(0));
+        acc[0].fold();
     }
     edge_elements(head, npack * V, n, [&](int64_t i) {
         reduce_term<MODE, EXACT>(acc[0], widen(x[i]), MODE == kRedDot ? widen(y[i]) : C(0));

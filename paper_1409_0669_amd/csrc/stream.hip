@@ -182,7 +182,7 @@ __global__ __launch_bounds__(1024) void k_cg(int64_t n, compute_t<T> a, const co
     r += head;
     q += head;
     n -= head;
-    Acc<C, COMP> acc[U];
+    cg_acc_t<C, COMP> acc[U];
     const int64_t npack = n / V;
     Range rg = pack_range(npack, inc);
     int64_t i = rg.begin;
@@ -222,6 +222,7 @@ __global__ __launch_bounds__(1024) void k_cg(int64_t n, compute_t<T> a, const co
             C rn = widen(vr.v[e]);
             acc[0].template add_prod<EXACT>(rn, rn);
         }
+        acc[0].fold();
         store_pack_nt<T, V>(x + o, vx);
         store_pack_nt<T, V>(r + o, vr);
     }
