@@ -1898,12 +1898,18 @@ bwla_status bwla_batch_plan_create(bwla_dtype t, bwla_acc acc, bwla_dtype out_t,
         while (lanes < 64 && lanes < packs)
             lanes <<= 1;
         b.lanes = lanes;
+        const bool shared = tile && q.n > long_from(es);
+        if (shared) {
+            b.mode = kModeLong;
+            b.lanes = long_rows(q.n);
+        }
         if (q.m == 0)
             continue;
         int64_t rpi = std::max<int64_t>(1, std::min<int64_t>(q.m, kTileElems / std::max<int64_t>(1, q.n)));
         if (tile) {
             // whole passes: a wave carries kTileRows * 64 / lanes rows at a time
-            const int64_t wave_rows = kTileRows * (64 / lanes), group_rows = wave_rows * (p->block / 64);
+            const int64_t wave_rows = shared ? b.lanes : kTileRows * (64 / lanes);
+            const int64_t group_rows = shared ? wave_rows : wave_rows * (p->block / 64);
             rpi = rpi >= group_rows ? rpi / group_rows * group_rows : std::max(wave_rows, rpi / wave_rows * wave_rows);
         }
         for (int64_t r0 = 0; r0 < q.m; r0 += rpi) {

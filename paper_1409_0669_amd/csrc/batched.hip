@@ -223,6 +223,10 @@ __device__ __forceinline__ void gemv_tile_rows(const BatchGemv &g, int64_t rb, i
     constexpr bool EXACT = std::is_same<T, bf16_t>::value;
     constexpr int V = 16 / (int)sizeof(T), R = kTileRows, RPW = 64 / G;
     constexpr bool NT = G == 64;
+    // Plain sums of rows that share a wave have 8 packs per lane at most: one running sum. Up to
+    // long_from entries, one for the even and one for the odd elements of a pack.
+    constexpr int H = !COMP && G == 64 ? 2 : 1;
+    using Sum = std::conditional_t<!COMP, Acc<compute_t<T>, false>, acc_t<T, COMP>>;
     const int64_t n = g.n;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
     const int sub = lane / G, gl = lane % G;
@@ -241,9 +245,7 @@ __device__ __forceinline__ void gemv_tile_rows(const BatchGemv &g, int64_t rb, i
             const int64_t r = base + j * RPW + sub;
             row[j] = A + (r < re ? r : re - 1) * g.lda;
         }
-        // (a lane has at most 8 packs of rows that share a wave: one running sum)
-        std::conditional_t<!COMP && G < 64, Acc<compute_t<T>, false>, acc_t<T, COMP>> acc[R];
-        int taken = 0; // trips: packs of a row by this lane
+        Sum acc[H][R];
         for (int64_t k = gl * V; k < whole; k += G * V) {
             Pack<T, V> a[R];
             const Pack<T, V> xv = load_pack<T, V>(x + k);
@@ -255,11 +257,7 @@ __device__ __forceinline__ void gemv_tile_rows(const BatchGemv &g, int64_t rb, i
             for (int e = 0; e < V; ++e)
 #pragma unroll
                 for (int j = 0; j < R; ++j)
-                    acc[j].template add_prod<EXACT>(widen(a[j].v[e]), widen(xv.v[e]));
-            if (++taken % kRunPacks<T> == 0)
-#pragma unroll
-                for (int j = 0; j < R; ++j)
-                    acc[j].fold();
+                    acc[e % H][j].template add_prod<EXACT>(widen(a[j].v[e]), widen(xv.v[e]));
         }
         if (whole < n) {
             Pack<T, V> a[R];
@@ -273,13 +271,13 @@ __device__ __forceinline__ void gemv_tile_rows(const BatchGemv &g, int64_t rb, i
                 const T xe = e >= skip ? xv.v[e] : T(0);
 #pragma unroll
                 for (int j = 0; j < R; ++j)
-                    acc[j].template add_prod<EXACT>(widen(e >= skip ? a[j].v[e] : T(0)), widen(xe));
+                    acc[e % H][j].template add_prod<EXACT>(widen(e >= skip ? a[j].v[e] : T(0)), widen(xe));
             }
         }
         DD d[R];
 #pragma unroll
         for (int j = 0; j < R; ++j)
-            d[j] = acc[j].to_dd();
+            d[j] = H == 2 ? combine<COMP>(acc[0][j].to_dd(), acc[H - 1][j].to_dd()) : acc[0][j].to_dd();
         constexpr int B = G == 64 ? 5 : G == 32 ? 4 : G == 16 ? 3 : 2; // highest lane bit of a group
         halve<COMP, B, 4>(d, lane);
         halve<COMP, B - 1, 2>(d, lane);
@@ -294,6 +292,110 @@ __device__ __forceinline__ void gemv_tile_rows(const BatchGemv &g, int64_t rb, i
         const int64_t r = base + j * RPW + sub;
         if (gl % (G / 8) == 0 && r < re)
             store_out(g.y, r, out_f64, d[0].hi + d[0].lo);
+    }
+}
+
+// Rows of more than long_from entries: the work-group shares R of them, each
+// thread U packs of each in flight (R * U = 8), and the waves' sums are added in wave order
+// through LDS.  A tile of such rows has too few of them to give every wave 8 of
+// its own: with one wave's 8 rows per tile three of four waves were idle and each row
+// was one serial chain.  GPU time of 8 GEMVs of 300
+// rows, a wave's rows -> this: 4099 f32 14.9 -> 10.6 us, 16384 f32 47 -> 28, 10^5 f32 294 ->
+// 173, 5000 compensated bf16 14.3 -> 11, 16384 f64 97 -> 58; of 4 of 40 rows of 10^6 f32 2620 -> 159.
+template <typename T, bool COMP, int R>
+__device__ __forceinline__ void gemv_tile_long(const BatchGemv &g, int64_t rb, int64_t re, int out_f64, DD *lds)
+{
+    constexpr bool EXACT = std::is_same<T, bf16_t>::value;
+    constexpr int V = 16 / (int)sizeof(T), U = 8 / R;
+    const int64_t n = g.n, kpack = n / V, tail = n - kpack * V;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    const int64_t step = blockDim.x;
+    const T *A = (const T *)g.A;
+    const T *x = (const T *)g.x;
+    for (int64_t base = rb; base < re; base += R) {
+        const T *row[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) // rows past the tile re-read its last one and are not stored
+            row[r] = A + (base + r < re ? base + r : re - 1) * g.lda;
+        acc_t<T, COMP> acc[R];
+        int taken = 0; // packs of a row by this thread
+        auto fold = [&](int packs) {
+            taken += packs;
+            if (taken % kRunPacks<T> == 0)
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+                    acc[r].fold();
+        };
+        int64_t p = threadIdx.x;
+        for (; p + (U - 1) * step < kpack; p += U * step) {
+            Pack<T, V> a[U][R], xv[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                xv[u] = load_pack<T, V>(x + (p + u * step) * V);
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+                    a[u][r] = load_pack_nt<T, V>(row[r] + (p + u * step) * V);
+            }
+            end_of_loads();
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+#pragma unroll
+                for (int e = 0; e < V; ++e)
+#pragma unroll
+                    for (int r = 0; r < R; ++r)
+                        acc[r].template add_prod<EXACT>(widen(a[u][r].v[e]), widen(xv[u].v[e]));
+                fold(1);
+            }
+        }
+        for (; p < kpack; p += step) {
+            Pack<T, V> a[R];
+            const Pack<T, V> xv = load_pack<T, V>(x + p * V);
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                a[r] = load_pack_nt<T, V>(row[r] + p * V);
+#pragma unroll
+            for (int e = 0; e < V; ++e)
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+                    acc[r].template add_prod<EXACT>(widen(a[r].v[e]), widen(xv.v[e]));
+            fold(1);
+        }
+        if (threadIdx.x < tail) {
+            const int64_t k = kpack * V + threadIdx.x;
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                acc[r].template add_prod<EXACT>(widen(row[r][k]), widen(x[k]));
+        }
+        // the rows' sums over the wave together, as in gemv_tile_rows: lanes of
+        // one R-th of the wave end with one row's
+        DD d[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            d[r] = acc[r].to_dd();
+        if constexpr (R > 1) {
+            halve<COMP, 5, R / 2>(d, lane);
+            halve<COMP, 4, R / 4>(d, lane);
+            if constexpr (R == 8)
+                halve<COMP, 3, 1>(d, lane);
+            else
+                d[0] = combine<COMP>(d[0], dpp_dd<kDppXor8>(d[0]));
+            d[0] = combine<COMP>(d[0], dpp_dd<kDppHalfMirror>(d[0]));
+            d[0] = combine<COMP>(d[0], dpp_dd<kDppXor2>(d[0]));
+            d[0] = combine<COMP>(d[0], dpp_dd<kDppXor1>(d[0]));
+        } else {
+            d[0] = wave_sum<COMP>(d[0]);
+        }
+        if (lane % (64 / R) == 0)
+            lds[wave * R + lane / (64 / R)] = d[0];
+        __syncthreads();
+        if (threadIdx.x < R) {
+            DD t = lds[threadIdx.x];
+            for (int w = 1; w < nw; ++w)
+                t = combine<COMP>(t, lds[w * R + threadIdx.x]);
+            if (base + threadIdx.x < re)
+                store_out(g.y, base + threadIdx.x, out_f64, t.hi + t.lo);
+        }
+        __syncthreads(); // lds is written again by the next rows
     }
 }
 
@@ -356,7 +458,7 @@ template <typename T, bool COMP>
 __global__ __launch_bounds__(512) void k_grouped(BatchArgs a)
 {
     constexpr int NATIVE = 16 / (int)sizeof(T);
-    __shared__ DD lds[16];
+    __shared__ DD lds[64]; // block_sum's, or 8 waves' sums of 8 rows
     // the item is the same for every thread of the work-group
     const BatchItem w = a.items[blockIdx.x];
     if (__builtin_amdgcn_readfirstlane(w.kind) == 1) { // block_sum holds barriers
@@ -367,8 +469,17 @@ __global__ __launch_bounds__(512) void k_grouped(BatchArgs a)
         return;
     }
     const BatchGemv &g = a.gemv[w.prob];
-    if (__builtin_amdgcn_readfirstlane(g.mode) == kModeScalar) {
+    const int mode = __builtin_amdgcn_readfirstlane(g.mode);
+    if (mode == kModeScalar) {
         gemv_tile_scalar<T, COMP>(g, w.begin, w.end, a.out_f64);
+        return;
+    }
+    if (mode == kModeLong) { // holds barriers: begin and end are the work-group's
+        switch (__builtin_amdgcn_readfirstlane(g.lanes)) {
+        case 8: gemv_tile_long<T, COMP, 8>(g, w.begin, w.end, a.out_f64, lds); break;
+        case 4: gemv_tile_long<T, COMP, 4>(g, w.begin, w.end, a.out_f64, lds); break;
+        default: gemv_tile_long<T, COMP, 1>(g, w.begin, w.end, a.out_f64, lds); break;
+        }
         return;
     }
     switch (__builtin_amdgcn_readfirstlane(g.lanes)) {

@@ -176,8 +176,16 @@ struct BatchItem {
 // plan-wide BatchArgs::vec instead).
 enum {
     kModePacked = 0, // 16-byte packs of every operand (elements aligned to their size)
-    kModeScalar = 1  // one element per access
+    kModeScalar = 1, // one element per access
+    kModeLong = 2    // GEMV: packs, a work-group shares rows of more than long_from() entries
 };
+// Where a tile of 2^16 entries has too few rows for the waves to have their own
+// (8 GEMVs of 300 rows, own -> shared: f64 2500 entries 18.2 -> 20.6 us, 3000 21.3 -> 18.6, f32 9.9 ->
+// 13.0, 11.9 -> 10.7, bf16 3000 9.1 -> 9.4, 4096 10.7 -> 10.0), for elements of `es` bytes.
+inline int64_t long_from(size_t es) { return es >= 4 ? 2816 : 4096; }
+// Rows that a work-group shares at once: a tile of 2^16 entries holds 8 of up
+// to 2^13 entries; longer rows, fewer, so that few rows still make many tiles.
+inline int long_rows(int64_t n) { return n <= 8192 ? 8 : n <= 32768 ? 4 : 1; }
 constexpr int kTileRows = 8;  // rows a lane group of a packed GEMV tile carries at once
 constexpr int kRowPacks = 16; // default packs of a row each lane of a packed tile owns (sets its row-group size)
 struct BatchGemv {
@@ -185,7 +193,7 @@ struct BatchGemv {
     int64_t m, n, lda;
     const void *x;
     void *y;
-    int32_t lanes; // lanes per row (power of two, <= 64; grouped launch, packs: 8 at least)
+    int32_t lanes; // lanes per row (power of two, <= 64; grouped launch, packs: 8 at least); kModeLong: long_rows
     int32_t mode;  // kMode*
 };
 struct BatchDot {
