@@ -255,6 +255,10 @@ Cfg resolve_vector(int op, int t, int acc, int64_t n, std::initializer_list<cons
     return c;
 }
 
+// Bytes per microsecond that a CU streams from HBM when all of them do (7.2 TB/s over
+// 256); the shape rules below count work-groups in CUs of the device at hand.
+constexpr double kCuRate = 7.2e6 / 256;
+
 // A launch holds fewer than 2^32 threads.
 bool too_many_threads(int64_t groups, int block) { return (double)groups * block >= 4294967296.0; }
 
@@ -272,11 +276,11 @@ bool too_many_threads(int64_t groups, int block) { return (double)groups * block
 void few_lines(Cfg &c, int t, bool comp, int64_t L, int64_t K, int64_t packs)
 {
     const double bytes = (double)L * K * dsize(t);
-    const int64_t cus = 256;
+    const int64_t cus = device_cus();
     const bool large = bytes >= 268435456.0;
     auto cost = [&](int64_t groups, int64_t split) {
         const double n = (double)groups * (double)split;
-        const double us = bytes / 7.2e6 * ceil(n / cus) * cus / n;
+        const double us = bytes / (kCuRate * (double)cus) * ceil(n / (double)cus) * (double)cus / n;
         return split > 1 ? us + 2.0 + 0.08 * (double)std::min<int64_t>(split, 8) + 0.012 * (double)split : us;
     };
     const int64_t groups = ceil_div(L, c.rows);
@@ -285,7 +289,7 @@ void few_lines(Cfg &c, int t, bool comp, int64_t L, int64_t K, int64_t packs)
     if (L >= 512 && !large) {
         if (c.rows > 1 && cost(L, 1) < 0.9 * cost(groups, 1)) {
             c.rows = 1;
-            c.block = (int)std::min<int64_t>(c.block, 64 * ceil_div(2048, L));
+            c.block = (int)std::min<int64_t>(c.block, 64 * ceil_div(8 * cus, L));
         }
         return;
     }
@@ -376,7 +380,8 @@ Cfg rows_rule(int t, int acc, int64_t L, int64_t K, bool with_dot)
         else if (packs <= 64 && L >= 8192)
             c.rows = 4;
         const int64_t groups = std::max<int64_t>(1, ceil_div(L, c.rows));
-        int64_t waves = groups < 3000 ? ceil_div(2048, groups) : packs < 1500 ? 2 : 4;
+        const int64_t cus = device_cus();
+        int64_t waves = groups < 3000 * cus / 256 ? ceil_div(8 * cus, groups) : packs < 1500 ? 2 : 4;
         waves = std::min<int64_t>({waves, ceil_div(packs, 64), 16});
         c.block = (int)(64 * waves);
     }
@@ -473,6 +478,7 @@ Cfg cols_rule(int t, int acc, int64_t L, int64_t K, int vec, bool line_aligned)
     const bool comp = acc == BWLA_ACC_COMPENSATED, f64 = t == BWLA_F64;
     const int native = native_vec(t);
     const double bytes = (double)L * K * dsize(t);
+    const int64_t cus = device_cus();
     Cfg c{};
     auto tiles_of = [&](int lines) {
         c.rows = lines;
@@ -492,7 +498,7 @@ Cfg cols_rule(int t, int acc, int64_t L, int64_t K, int vec, bool line_aligned)
     const int pack = std::min(native, 4);
     if (vec < native || K < native) {
         const int v = std::min(vec, t == BWLA_BF16 && K > 1 ? 2 : 1);
-        const int64_t fill = (bytes < 32.0 * (1 << 20) ? 256 : 1024) / std::max<int64_t>(1, ceil_div(K, 64 * v));
+        const int64_t fill = (bytes < 32.0 * (1 << 20) ? 1 : 4) * cus / std::max<int64_t>(1, ceil_div(K, 64 * v));
         one_line(v, comp && f64 ? 1024 : 512, 16, std::max<int64_t>(1, std::min<int64_t>(fill, L / 128)));
     } else if (L < 40 || (L <= 128 && bytes >= 256.0 * (1 << 20))) {
         const bool small = bytes < 32.0 * (1 << 20);
@@ -501,19 +507,19 @@ Cfg cols_rule(int t, int acc, int64_t L, int64_t K, int vec, bool line_aligned)
             v /= 2;
         one_line(v, small ? (int)(64 * std::max<int64_t>(1, std::min<int64_t>(8, ceil_div(L, 4)))) : 64, small && L >= 4 ? 4 : 2, 1);
     } else if (narrow > 1 && (narrow == 8 || 4 * K <= 3 * (64 / narrow) * native)) {
-        const int64_t split = std::max<int64_t>(1, std::min<int64_t>(bytes < 8e6 ? 128 : 256, L / 64));
+        const int64_t split = std::max<int64_t>(1, std::min<int64_t>(bytes < 8e6 ? cus / 2 : cus, L / 64));
         c.rows = narrow;
         c.block = 512;
         c.unroll = f64 || (t == BWLA_F32 && !comp) ? 4 : 8;
         // a single slice, at a CU's rate, or the second kernel
-        c.split = bytes / 7.2e6 * 256.0 < bytes / 7.2e6 * 256.0 / (double)split + 2.5 ? 1 : (int)split;
+        c.split = bytes / kCuRate < bytes / kCuRate / (double)split + 2.5 ? 1 : (int)split;
     } else if (!comp && line_aligned && t != BWLA_BF16 && bytes >= (f64 ? 64.0 : 1024.0) * (1 << 20) && L >= 512 &&
                K >= 128 * (int64_t)(8 / dsize(t))) {
         const bool large = f64 && bytes >= 1073741824.0;
         c.vec = (int)(8 / dsize(t));
         c.unroll = 4;
         c.block = large ? 512 : 1024;
-        c.split = (int)std::min<int64_t>(ceil_div(large ? 512 : 256, tiles_of(1)), std::max<int64_t>(1, L / 16));
+        c.split = (int)std::min<int64_t>(ceil_div(large ? 2 * cus : cus, tiles_of(1)), std::max<int64_t>(1, L / 16));
     } else {
         // the cost of 512-, 256- and 128-byte segments
         static const double kSegment[3][3] = {{1.0, 1.05, 1.12}, {1.02, 1.01, 1.08}, {1.0, 1.08, 1.15}};
@@ -525,10 +531,10 @@ Cfg cols_rule(int t, int acc, int64_t L, int64_t K, int vec, bool line_aligned)
         for (int i = 0; i < 3; ++i) {
             const int64_t tiles = tiles_of(2 << i);
             for (int64_t fill = 0; fill <= 4; ++fill) { // one slice, or as many as fill the chip 1 to 4 times
-                const int64_t split = std::max<int64_t>(1, std::min(fill * 256 / tiles, L / 64));
+                const int64_t split = std::max<int64_t>(1, std::min(fill * cus / tiles, L / 64));
                 const double groups = (double)tiles * (double)split;
-                const double uneven = ceil(groups / 256.0) * 256.0 / groups;
-                double us = bytes / 7.2e6 * segment[i] * uneven;
+                const double uneven = ceil(groups / (double)cus) * (double)cus / groups;
+                double us = bytes / (kCuRate * (double)cus) * segment[i] * uneven;
                 if (split > 1)
                     us += 2.0 + 0.08 * (double)std::min<int64_t>(split, 8) + 0.02 * (double)split;
                 if (us < best) {
