@@ -8,6 +8,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -74,19 +75,17 @@ int native_vec(int t) { return (int)(16 / dsize(t)); }
 // ---------------------------------------------------------------------------
 int device_cus()
 {
-    static std::mutex mu;
-    static int cached[64] = {0};
+    static std::atomic<int> cached[64];
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64)
         return 256;
-    std::lock_guard<std::mutex> lk(mu);
-    if (!cached[dev]) {
-        int cus = 0;
+    int cus = cached[dev].load(std::memory_order_relaxed);
+    if (!cus) {
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
             cus = 256;
-        cached[dev] = cus;
+        cached[dev].store(cus, std::memory_order_relaxed);
     }
-    return cached[dev];
+    return cus;
 }
 
 // ---------------------------------------------------------------------------
@@ -273,10 +272,9 @@ bool too_many_threads(int64_t groups, int block) { return (double)groups * block
 // 129, 1000 x 200000 130 -> 117.
 // 512 lines and more of less than 256 MiB stay whole, with a work-group each where
 // that fills the CUs better (600 x 13333 10.8 -> 10.0).
-void few_lines(Cfg &c, int t, bool comp, int64_t L, int64_t K, int64_t packs)
+void few_lines(Cfg &c, int t, bool comp, int64_t L, int64_t K, int64_t packs, int64_t cus)
 {
     const double bytes = (double)L * K * dsize(t);
-    const int64_t cus = device_cus();
     const bool large = bytes >= 268435456.0;
     auto cost = [&](int64_t groups, int64_t split) {
         const double n = (double)groups * (double)split;
@@ -293,6 +291,8 @@ void few_lines(Cfg &c, int t, bool comp, int64_t L, int64_t K, int64_t packs)
         }
         return;
     }
+    if (!large && cost(groups, 1) < 2.0) // less than a second kernel
+        return;
     int rows = bytes < 1.6e7 ? 1 : bytes < 1.28e8 || (comp && t == BWLA_F32) ? 2 : 4;
     while (rows > 1 && rows > L + L / 3) // 3 lines take 4
         rows /= 2;
@@ -348,6 +348,7 @@ Cfg rows_rule(int t, int acc, int64_t L, int64_t K, bool with_dot)
 {
     const bool comp = acc == BWLA_ACC_COMPENSATED;
     const double bytes = (double)L * K * dsize(t), mib = 1 << 20;
+    const int64_t cus = device_cus();
     Cfg c{};
     c.vec = native_vec(t);
     c.rows = c.unroll = 2;
@@ -380,14 +381,13 @@ Cfg rows_rule(int t, int acc, int64_t L, int64_t K, bool with_dot)
         else if (packs <= 64 && L >= 8192)
             c.rows = 4;
         const int64_t groups = std::max<int64_t>(1, ceil_div(L, c.rows));
-        const int64_t cus = device_cus();
         int64_t waves = groups < 3000 * cus / 256 ? ceil_div(8 * cus, groups) : packs < 1500 ? 2 : 4;
         waves = std::min<int64_t>({waves, ceil_div(packs, 64), 16});
         c.block = (int)(64 * waves);
     }
     if (packs <= 64 && L > 1 << 20)
         c.rows = 8;
-    few_lines(c, t, comp, L, K, packs);
+    few_lines(c, t, comp, L, K, packs, cus);
     if (with_dot && bytes >= 256 * mib && L >= 2048)
         c.rows = std::max(c.rows, 4);
     c.block = (int)std::min<int64_t>(c.block, ceil_div(ceil_div(packs, c.split), 64) * 64);
