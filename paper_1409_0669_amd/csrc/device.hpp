@@ -292,21 +292,21 @@ struct AccF64 {
 // Plain accumulator of a sum in short runs, so that the error does not grow with
 // the terms of a thread, and the number of threads that share a sum can follow
 // speed alone: a run is summed in the compute precision, and fold() adds it to the
-// thread's sum, in float64 also for float32.  A run is one pack of f32, two of bf16,
-// four of f64, or four lines.  Error of GEMV rows before the output is rounded
+// thread's sum, in float64 also for float32 (S).  A run is one pack of f32, two of bf16,
+// four of f64, or a trip's lines.  Error of GEMV rows before the output is rounded
 // (root mean square, in units of 2^-24 or 2^-53 of a random sum's size), one running sum
 // per thread -> this: 4096 x 4096 f32 2.5 -> 0.67, bf16 0.74 -> 0.31, f64 2.7 -> 1.8; 2048 x
 // 16384 f32 3.3 -> 0.67; 100 x 640000 f64 11 -> 2.3.  GPU time within 2 %.
-template <typename C> struct AccFold {
+template <typename C, typename S = double> struct AccFold {
     C t = 0;
-    double s = 0;
+    S s = 0;
     template <bool EXACT_PROD> __device__ __forceinline__ void add_prod(C a, C b) { t = fma_c(a, b, t); }
     __device__ __forceinline__ void fold()
     {
-        s += (double)t;
+        s += (S)t;
         t = 0;
     }
-    __device__ __forceinline__ DD to_dd() const { return DD{s + (double)t, 0.0}; }
+    __device__ __forceinline__ DD to_dd() const { return DD{(double)s + (double)t, 0.0}; }
 };
 template <typename T> constexpr int kRunPacks = sizeof(T) == 8 ? 4 : sizeof(T) == 4 ? 1 : 2;
 constexpr int kRunLines = 4;
@@ -317,6 +317,12 @@ using acc_t = std::conditional_t<!COMP, AccFold<compute_t<T>>,
 // The compensated CG update keeps the float32 form: four streams per term, and
 // the conversions would sit between a trip's loads.
 template <typename C, bool COMP> using cg_acc_t = std::conditional_t<COMP, Acc<C, true>, AccFold<C>>;
+// The cols kernel with several lines per access adds a trip's lines to a sum in the compute
+// precision: its 4 or 8 outputs per lane would take as many conversions per trip, with one
+// wave per SIMD to hide them (4096 x 4096 f32 15.9 us, 15.7 so; error 0.67 and 1.3 of the
+// units above, 2.4 as one running sum).
+template <typename T, bool COMP>
+using trip_acc_t = std::conditional_t<!COMP, AccFold<compute_t<T>, compute_t<T>>, acc_t<T, COMP>>;
 // The cols kernel with one line per access, where one wave may take all lines:
 // a float64 sum of exact products for float32.
 template <typename T, bool COMP>

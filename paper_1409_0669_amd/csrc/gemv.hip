@@ -395,7 +395,7 @@ __global__ __launch_bounds__(1024) void k_gemv_cols_grouped(int64_t L, int64_t K
         const int64_t k = (q0 + V <= K ? q0 : K - V) + t % V;
         return k < q0 || q0 >= K ? -1 : k;
     };
-    acc_t<T, COMP> acc[V];
+    trip_acc_t<T, COMP> acc[V];
     if constexpr (UNIT)
         incv = 1;
     const T *vt = v + lb * incv;
@@ -423,7 +423,7 @@ __global__ __launch_bounds__(1024) void k_gemv_cols_grouped(int64_t L, int64_t K
 #pragma unroll
             for (int e = 0; e < V; ++e) {
                 acc[e].template add_prod<EXACT>(widen(a[u].v[e]), widen(xv.v[u]));
-                if (u % kRunLines == kRunLines - 1)
+                if (u == U - 1)
                     acc[e].fold();
             }
     }
@@ -443,7 +443,7 @@ __global__ __launch_bounds__(1024) void k_gemv_cols_grouped(int64_t L, int64_t K
 #pragma unroll
                 for (int e = 0; e < V; ++e) {
                     acc[e].template add_prod<EXACT>(widen(a[u].v[e]), widen(xv[u]));
-                    if (u % kRunLines == kRunLines - 1)
+                    if (u == U - 1)
                         acc[e].fold();
                 }
     }
