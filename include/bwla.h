@@ -104,14 +104,15 @@ typedef enum BWLA_ENUM_INT {
  *                     line in flight: 1 or 2), split (blocks along a line), grid
  *   GEMV_COLS:        block, vec, unroll (lines in flight), split (blocks across
  *                     lines), grid, rows (lines per wave access; above 1 the
- *                     packs are 16 bytes wide).  An entry with no block,
- *                     unroll, split, grid and rows leaves all of them to a
- *                     rule that follows the matrix's shape
+ *                     packs are 16 bytes wide)
+ *                     A GEMV entry with no block, unroll, split, grid and rows
+ *                     leaves all of them to a rule that follows the matrix's
+ *                     shape
  *   GER:              block, vec, rows
  *   BATCH:            block (work-group size, at most 512), unroll (packs of a
  *                     GEMV row each lane of a tile owns, 8 at most: sets how
- *                     many lanes, 8 to 64, share a row of less than 4 KiB); its size class is that of the plan's
- *                     algorithmic bytes
+ *                     many lanes, 8 to 64, share a row of less than 4 KiB);
+ *                     its size class is that of the plan's algorithmic bytes
  * block:  threads per work-group, a multiple of 64 in [64, 1024]
  * vec:    consecutive elements per thread per access: 1, 2, 4, 8 or 16 (the
  *         paper's vector data types); widths above 16 bytes are issued as
@@ -342,7 +343,7 @@ bwla_status bwla_workspace_size(bwla_op op, bwla_dtype t, bwla_acc acc, bwla_lay
  * (cfg->unroll, a power of two up to 32); other fields are ignored.  A zero
  * (or NULL) field takes the configuration table's BWLA_OP_BATCH entry for
  * (t, acc, size class of the plan's algorithmic bytes), else the defaults
- * (256 threads, 16 packs per lane).
+ * (256 threads, 16 packs per lane; more than 8 packs act as 8).
  * (The library also holds a persistent work-queue form of this launch, a
  * machine-sized grid drawing items from an atomic counter.  It has not been
  * validated on hardware and is switched off: with

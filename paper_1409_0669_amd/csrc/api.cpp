@@ -462,7 +462,8 @@ Cfg resolve_rows(int t, int acc, int64_t L, int64_t K, const void *A, const void
 //
 // One line per access (k_gemv_cols) stays where it is the faster: plain f64
 // from 64 MiB and f32 from 1 GiB with lines on cache lines, 8 bytes per lane
-// (f64 16384 x 16384 298 us against 308, f32 151 against 155).
+// (f64 16384 x 16384 298 us against 308, f32 151 against 155), 512 lines and two tiles (128
+// f64 or 256 f32 columns) at least, with fewer of which most of its waves have no line.
 //
 // The ends of the range, where most of a tile or of a work-group has no data (GPU times
 // of 60 MB with the choice above -> this one):
@@ -470,7 +471,7 @@ Cfg resolve_rows(int t, int acc, int64_t L, int64_t K, const void *A, const void
 //    (two for bf16), 16 lines in flight (f32 5e6 x 3 1292 us -> 110, bf16 4.3e6 x 7 1847 -> 117).
 //  - Lines that leave a quarter of their tile empty: the narrowest tile that holds
 //    them, one slice per CU (f64 3.75e6 x 2 176 -> 40, bf16 9e5 x 33 60 -> 27).
-//  - Fewer than 40 lines, up to 128 of long ones: one line per access and one wave per
+//  - Fewer than 40 lines, up to 128 from 256 MiB on: one line per access and one wave per
 //    work-group (of small matrices one for four lines), f32 1 x 1.5e7 210 -> 35, compensated 8 x
 //    1.9e6 52 -> 16, 16 x 9.4e5 30 -> 14; f64 100 x 500000 107 -> 62.
 Cfg cols_rule(int t, int acc, int64_t L, int64_t K, int vec, bool line_aligned)

@@ -300,7 +300,7 @@ __device__ __forceinline__ void gemv_tile_rows(const BatchGemv &g, int64_t rb, i
 // through LDS.  A tile of such rows has too few of them to give every wave 8 of
 // its own: with one wave's 8 rows per tile three of four waves were idle and each row
 // was one serial chain.  GPU time of 8 GEMVs of 300
-// rows, a wave's rows -> this: 4099 f32 14.9 -> 10.6 us, 16384 f32 47 -> 28, 10^5 f32 294 ->
+// rows, a wave's rows -> this: 4099 f32 14.9 -> 11.9 us, 16384 f32 47 -> 28, 10^5 f32 294 ->
 // 173, 5000 compensated bf16 14.3 -> 11, 16384 f64 97 -> 58; of 4 of 40 rows of 10^6 f32 2620 -> 159.
 template <typename T, bool COMP, int R>
 __device__ __forceinline__ void gemv_tile_long(const BatchGemv &g, int64_t rb, int64_t re, int out_f64, DD *lds)

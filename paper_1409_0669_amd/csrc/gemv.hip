@@ -40,8 +40,9 @@
 namespace bwla {
 
 // The prior value of output i (read only when it is updated), and the store
-// of result v in its place.  Kernels fetch the prior value before their main
-// loop, where its latency is hidden.
+// of result v in its place.  The rows kernel fetches the prior value before its
+// main loop, the grouped cols kernel before its sums across lanes and waves, and the line
+// combine with its partials; the one-line cols kernel at the store.
 __device__ __forceinline__ double out_prior(const GemvOut &o, int64_t i)
 {
     if (o.mode != kOutUpdate)

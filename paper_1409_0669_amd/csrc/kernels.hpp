@@ -158,7 +158,7 @@ hipError_t launch_combine_scalar(const void *partials, int64_t count, bool comp,
 // out[o] = sum over q < split of partials[((o / G) * split + q) * G + o % G],
 // for o < outputs: the slices of a split GEMV combined in slice order.  With
 // w != NULL, work-group b also writes dparts[b] = sum of w[o] * out[o] over
-// its 256 outputs.
+// its combine_lines_outputs(split) outputs.
 hipError_t launch_combine_lines(const void *partials, int64_t outputs, int64_t G, int64_t split,
                                 bool comp, const GemvOut &out, const void *w, void *dparts,
                                 hipStream_t s);
@@ -187,7 +187,9 @@ inline int64_t long_from(size_t es) { return es >= 4 ? 2816 : 4096; }
 // to 2^13 entries; longer rows, fewer, so that few rows still make many tiles.
 inline int long_rows(int64_t n) { return n <= 8192 ? 8 : n <= 32768 ? 4 : 1; }
 constexpr int kTileRows = 8;  // rows a lane group of a packed GEMV tile carries at once
-constexpr int kRowPacks = 16; // default packs of a row each lane of a packed tile owns (sets its row-group size)
+// Default packs of a row each lane of a packed tile owns (sets its row-group size; plans take
+// more than 8 as 8).
+constexpr int kRowPacks = 16;
 struct BatchGemv {
     const void *A;
     int64_t m, n, lda;
@@ -220,7 +222,8 @@ hipError_t launch_batch_reset(unsigned *counters, int64_t count, hipStream_t s);
 // One work-group per item (a.n_items work-groups of `block` threads).
 template <typename T>
 hipError_t launch_grouped(const BatchArgs &a, bool comp, int block, hipStream_t s);
-// Combines the chunk partials of every multi-chunk dot, in chunk order.
+// Combines the chunk partials of every multi-chunk dot: each lane of a wave every 64th in chunk
+// order, then the lanes.
 hipError_t launch_batch_finalize(const BatchDot *dots, int64_t nd, const double *partials, bool comp,
                                  int out_f64, hipStream_t s);
 

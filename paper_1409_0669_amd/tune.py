@@ -393,8 +393,8 @@ def _cols_candidates(dtype, quick, cus=256):
     grouped = [dict(block=b, vec=native, unroll=u, split=0, grid=g * cus, rows=r) for b in (256, 512) for u in (4, 8)
                for r in (2, 4, 8) for g in GEMV_GROUPS_PER_CU]
     # one line per access; one element per lane included: with few outputs
-    # the split (and the second kernel) grows with the pack width.  16 and 32
-    # lines in flight only where the library takes them (at most 128 bytes of
+    # the split (and the second kernel) grows with the pack width.  16 lines
+    # in flight only where the library takes them (at most 128 bytes of
     # A per lane in flight)
     single = [dict(block=b, vec=v, unroll=u, split=0, grid=g * cus, rows=1) for b in (512, 1024) for v in vecs
               for u in (4, 8, 16) if u <= 8 or u * v * es <= 128 for g in GEMV_GROUPS_PER_CU]
